@@ -315,6 +315,20 @@ class Case final : public CaseBase {
         }
         auto zero = [&](int s) { return t.C[s] == R(0) && t.Gx[s] == R(0) && t.Gy[s] == R(0); };
         t.zero_diag = (zero(2) && zero(6) ? kZeroDiag26 : 0) | (zero(0) && zero(8) ? kZeroDiag08 : 0);
+        int n = 0;
+        for (int s = 0; s < NSLOT; ++s) {
+          if (zero(s)) continue;
+          if (n == NLIST) {
+            err = "a grid node has more than seven stencil entries";
+            return HLBM_E_ARG;
+          }
+          t.li_s[n] = s;
+          t.li_w[n][0] = t.C[s];
+          t.li_w[n][1] = t.Gx[s];
+          t.li_w[n][2] = t.Gy[s];
+          ++n;
+        }
+        for (; n < NLIST; ++n) t.li_s[n] = SELF_SLOT;
       }
       if (!grid_.mesh) {
         HIPCHK(upload(&tab_, tab.data(), tab.size() * sizeof(GridClass<R>)));

@@ -17,6 +17,12 @@ namespace mghlbm {
 constexpr int NSLOT = 9;
 constexpr int SELF_SLOT = 4;
 
+// Entries a split-quad stencil has at most: the node, its four axis
+// neighbours and two of the diagonal ones (each cell around it is cut along
+// one diagonal, and of a column of cells either the upper or the lower one's
+// diagonal ends in the node).
+constexpr int NLIST = 7;
+
 enum NodeType : int { NODE_INTERIOR = 0, NODE_INTERFACE = 1, NODE_WALL = 2 };
 
 // Per-structured-step scalars, computed once on the host in FP64 so the
@@ -46,6 +52,10 @@ struct GridClass {
   int type;         // NodeType
   int zero_diag;    // bit 0: slots 2 and 6 (the (+1,-1) and (-1,+1)
                     // neighbours) carry zero weights; bit 1: slots 0 and 8
+  // the same weights without the empty slots, in slot order: slot li_s[i]
+  // with (C, Gx, Gy) = li_w[i], padded with the node itself at zero weight
+  R li_w[NLIST][3];
+  int li_s[NLIST];
 };
 
 // slots a split-quad node lacks: the two diagonal neighbours across the

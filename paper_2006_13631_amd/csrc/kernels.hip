@@ -670,6 +670,183 @@ __device__ __forceinline__ void grid_substeps_block(
   }
 }
 
+// One node per lane for the whole launch (NT >= the region's nodes): the
+// lane keeps its node's populations, its seven stencil weights and the LDS
+// addresses of its seven neighbours in registers, so a sub-step is the
+// neighbour reads, the sums and the write of the new values, with no class
+// load and no index arithmetic. A lane whose node is no longer exact (or no
+// longer needed) sits out the remaining sub-steps. LDS holds the region and
+// the outer ring's structured-derived values node-major (a neighbour's
+// values are contiguous, so they are read in pairs, and consecutive lanes
+// are an odd number of words apart); with DB both exist twice, so one
+// address serves a copy's region and ring alike. Dealing the lanes afresh
+// over each sub-step's shrinking rectangle (grid_substeps_block) works on
+// fewer nodes, but pays a division per index, 21 weight loads from L1 and
+// bank conflicts where a row of the rectangle ends inside a wave: the
+// 2048^2 FP64 step (512 x 128 grid, 20 sub-steps) went from 0.168 to 0.158
+// ms and the FP32 one from 0.124 to 0.115 ms.
+template <class R, class G>
+constexpr size_t fixed_copy_elems() {
+  return (size_t)NS * (G::RN + G::NRING);
+}
+template <class R, class G>
+constexpr bool fixed_double_buffer() {
+  return 2 * sizeof(R) * fixed_copy_elems<R, G>() <= 160u * 1024u;
+}
+template <class R, class G, bool DB>
+constexpr size_t fixed_lds_bytes() {
+  return sizeof(R) * fixed_copy_elems<R, G>() * (DB ? 2 : 1);
+}
+
+template <class R, class G, int H, int NT, bool DB>
+__device__ __forceinline__ void grid_fixed_block(
+    const R *__restrict__ f, R *__restrict__ fout, const R *__restrict__ star_f, const int *__restrict__ ncode,
+    const GridClass<R> *__restrict__ tab, int nux, int nuy, int tiles_x, int t, R dt, R dt_tau,
+    const R *__restrict__ uw, int64_t k, int n_sub, int m0, int count, R *__restrict__ tape,
+    R *__restrict__ wtape, const int *__restrict__ widx, int nwall) {
+  constexpr int TX = G::TX, TY = G::TY, RX = G::RX, RN = G::RN;
+  static_assert(NT >= RN, "one node per lane");
+  constexpr int COPY = (int)fixed_copy_elems<R, G>(), RING = NS * RN;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  R *sl = reinterpret_cast<R *>(lds_raw);
+  const int idx = threadIdx.x, rx = idx % RX, ry = idx / RX;
+  const int x0 = (t % tiles_x) * TX - H, y0 = (t / tiles_x) * TY - H;  // region origin
+  const int gi = x0 + rx, gj = y0 + ry;
+  const bool in = idx < RN && gi >= 0 && gi < nux && gj >= 0 && gj < nuy;
+  const size_t N = (size_t)nux * nuy, p = in ? (size_t)gj * nux + gi : 0;
+  // the lamina velocity of every sub-step of the launch, read up front: a
+  // scalar load still in flight would hold up every later LDS wait
+  R uwv[H];
+#pragma unroll
+  for (int sub = 0; sub < H; ++sub) uwv[sub] = sub < count ? uw[k * n_sub + m0 + sub] : R(0);
+  R own[9], w[NLIST][3];
+  int row[NLIST];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) own[q] = in ? f[q * N + p] : R(0);
+  const int code = in ? ncode[p] : -1, typ = code & 3;
+  const GridClass<R> &cl = tab[code >= 0 ? code >> 4 : 0];
+  const bool iface = code >= 0 && typ == NODE_INTERFACE;
+  const int ring = idx < RN ? ring_slot<G>(gi, gj, rx, ry, nux, nuy) : -1;
+#pragma unroll
+  for (int i = 0; i < NLIST; ++i) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) w[i][a] = cl.li_w[i][a];
+    const int s = cl.li_s[i], di = s % 3 - 1, dj = s / 3 - 1;
+    row[i] = (idx + dj * RX + di) * NS;
+    if (iface) {
+      const int rs = ring_slot<G>(gi + di, gj + dj, rx + di, ry + dj, nux, nuy);
+      if (rs >= 0) row[i] = RING + rs * NS;
+    }
+  }
+  if (in) {
+    R P[3];
+    quad_moments<R>(own, P);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) sl[idx * NS + q] = own[q];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) sl[idx * NS + 9 + a] = P[a];
+    if (ring >= 0) {
+      R fs[9];
+#pragma unroll
+      for (int q = 0; q < 9; ++q) fs[q] = star_f[q * N + p];
+      quad_moments<R>(fs, P);
+#pragma unroll
+      for (int c = 0; c < (DB ? 2 : 1); ++c) {
+        R *r = sl + c * COPY + RING + ring * NS;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) r[q] = fs[q];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) r[9 + a] = P[a];
+      }
+      if (iface)  // an interpolation node's own term is its structured-derived value throughout
+#pragma unroll
+        for (int q = 0; q < 9; ++q) own[q] = fs[q];
+    }
+  }
+  __syncthreads();
+  // distance outside the tile: the lane's node is exact, and needed, up to
+  // sub-step count - 1 - out
+  const int out = max(max(H - rx, rx - (H + TX - 1)), max(max(H - ry, ry - (H + TY - 1)), 0));
+  const int last_sub = code >= 0 ? count - 1 - out : -1;
+  const bool tile = in && out == 0;
+#pragma unroll
+  for (int sub = 0; sub < H; ++sub) {
+    if (sub >= count) break;
+    const int cur = DB ? (sub & 1) * COPY : 0, nxt = DB ? COPY - cur : 0;
+    const bool act = sub <= last_sub;
+    R P[3];
+    R res[9];
+    if (act) {
+      // Eq.(ulbe) as in grid_substeps_block, slot by slot in the same order
+      R srho = R(0), sjx = R(0), sjy = R(0);
+#pragma unroll
+      for (int q = 0; q < 9; ++q) {
+        R a = R(0), ax = R(0), ay = R(0);
+#pragma unroll
+        for (int i = 0; i < NLIST; ++i) {
+          const R fq = sl[row[i] + cur + q];
+          a = fmad(w[i][0], fq, a);
+          if (CXd[q] != 0) ax = fmad(w[i][1], fq, ax);
+          if (CYd[q] != 0) ay = fmad(w[i][2], fq, ay);
+        }
+        srho += a;
+        if (CXd[q] != 0) sjx += R(CXd[q]) * a;
+        if (CYd[q] != 0) sjy += R(CYd[q]) * a;
+        res[q] = fmad(-dt_tau, a, fmad(dt, R(CXd[q]) * ax + R(CYd[q]) * ay, own[q]));
+      }
+      R pxx = R(0), pxy = R(0), pyy = R(0);
+#pragma unroll
+      for (int i = 0; i < NLIST; ++i) {
+        pxx = fmad(w[i][0], sl[row[i] + cur + 9], pxx);
+        pxy = fmad(w[i][0], sl[row[i] + cur + 10], pxy);
+        pyy = fmad(w[i][0], sl[row[i] + cur + 11], pyy);
+      }
+      const R base = fmad(R(-1.5), pxx + pyy, srho);
+#pragma unroll
+      for (int q = 0; q < 9; ++q) {
+        const R cx = R(CXd[q]), cy = R(CYd[q]);
+        const R cu = cx * sjx + cy * sjy;
+        const R cc = (cx * cx) * pxx + (R(2) * cx * cy) * pxy + (cy * cy) * pyy;
+        res[q] = fmad(dt_tau * wgt<R>(q), fmad(R(4.5), cc, fmad(R(3), cu, base)), res[q]);
+      }
+      if (typ == NODE_WALL) {  // impose the lamina velocity, keep rho and f^neq
+        R e[9], ew[9], r, vx, vy;
+        moments<R>(res, r, vx, vy);
+        if (wtape && tile) {  // taped for the adjoint: the moments before the velocity is imposed
+          R *wt = wtape + (size_t)(m0 + sub) * 3 * nwall;
+          const int wi = widx[p];
+          wt[wi] = r;
+          wt[nwall + wi] = vx;
+          wt[2 * nwall + wi] = vy;
+        }
+        equilibrium<R>(r, vx, vy, e);
+        equilibrium<R>(r, R(0), uwv[sub], ew);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) res[q] = ew[q] + (res[q] - e[q]);
+      }
+      quad_moments<R>(res, P);
+    }
+    if (!DB) __syncthreads();  // one copy: every read of the sub-step ends before the writes
+    if (act) {
+      if (sub + 1 < count) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) sl[nxt + idx * NS + q] = res[q];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sl[nxt + idx * NS + 9 + a] = P[a];
+      }
+      if (tile && (tape || sub + 1 == count)) {  // the tile is exact after every sub-step
+        R *dst = sub + 1 == count ? fout : tape + (size_t)(m0 + sub + 1) * 9 * N;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) dst[q * N + p] = res[q];
+      }
+      if (!iface)
+#pragma unroll
+        for (int q = 0; q < 9; ++q) own[q] = res[q];
+    }
+    if (sub + 1 < count) __syncthreads();
+  }
+}
+
 // Variants of the sub-step kernel: tile shape and workgroup size (one lane
 // per region node while staging). Variant 3's LDS fits two workgroups on a
 // CU in FP64 and more in FP32 (many small grids).
@@ -678,7 +855,14 @@ struct SubstepShape {
   using G = Region<TXv, TYv, Hv>;
   static constexpr int NT = NTv;
   static constexpr int H = Hv;  // sub-steps per launch, and the halo width
+  static constexpr bool FIXED = NTv >= G::RN;  // one node per lane for the whole launch
 };
+template <class R, class SV, bool BATCH = false>
+constexpr size_t variant_lds_bytes() {
+  using G = typename SV::G;
+  if constexpr (SV::FIXED) return fixed_lds_bytes<R, G, !BATCH && fixed_double_buffer<R, G>()>();
+  else return substeps_lds_bytes<R, G, !BATCH && substeps_double_buffer<R, G>()>();
+}
 template <int V>
 struct SubstepVariant;
 template <> struct SubstepVariant<0> : SubstepShape<16, 16, 576> {};
@@ -702,9 +886,14 @@ __global__ __launch_bounds__(SubstepVariant<V>::NT) void k_grid_substeps(
   using SV = SubstepVariant<V>;
   const int b = blockIdx.x;  // tiles are dealt to the eight XCDs in contiguous bands
   const int t = (ntiles % 8 == 0) ? (b % 8) * (ntiles / 8) + (b / 8) : b;
-  grid_substeps_block<R, typename SV::G, SV::H, SV::NT, substeps_double_buffer<R, typename SV::G>()>(
-      f, fout, star_f, star_n, ncode, tab, nux, nuy, tiles_x, t, dt, dt_tau, uw, *dk, n_sub, m0, count, tape, wtape,
-      widx, nwall);
+  if constexpr (SV::FIXED)
+    grid_fixed_block<R, typename SV::G, SV::H, SV::NT, fixed_double_buffer<R, typename SV::G>()>(
+        f, fout, star_f, ncode, tab, nux, nuy, tiles_x, t, dt, dt_tau, uw, *dk, n_sub, m0, count, tape, wtape, widx,
+        nwall);
+  else
+    grid_substeps_block<R, typename SV::G, SV::H, SV::NT, substeps_double_buffer<R, typename SV::G>()>(
+        f, fout, star_f, star_n, ncode, tab, nux, nuy, tiles_x, t, dt, dt_tau, uw, *dk, n_sub, m0, count, tape, wtape,
+        widx, nwall);
 }
 
 // launch m0 / kSubstepBlock of a batched step: item = (case, tile)
@@ -718,10 +907,16 @@ __global__ __launch_bounds__(SubstepVariant<V>::NT) void kb_grid_substeps(const 
   if (!batched_case(v, k)) return;
   const int cur = grid_cur(v, k), i = m0 / kSubstepBlock;
   const int tiles_x = (v.nux + SV::G::TX - 1) / SV::G::TX;
-  grid_substeps_block<R, typename SV::G, kSubstepBlock, SV::NT>(
-      v.grid[cur ^ (i & 1)], v.grid[cur ^ ((i + 1) & 1)], v.star_f, v.star_n, v.ncode, v.tab, v.nux, v.nuy, tiles_x,
-      it.y, v.dt_u, v.dt_over_tau_u, v.uw, k, v.n_sub, m0, min(kSubstepBlock, v.n_sub - m0), nullptr, nullptr,
-      nullptr, 0);
+  if constexpr (SV::FIXED)
+    grid_fixed_block<R, typename SV::G, kSubstepBlock, SV::NT, false>(
+        v.grid[cur ^ (i & 1)], v.grid[cur ^ ((i + 1) & 1)], v.star_f, v.ncode, v.tab, v.nux, v.nuy, tiles_x, it.y,
+        v.dt_u, v.dt_over_tau_u, v.uw, k, v.n_sub, m0, min(kSubstepBlock, v.n_sub - m0), nullptr, nullptr, nullptr,
+        0);
+  else
+    grid_substeps_block<R, typename SV::G, kSubstepBlock, SV::NT>(
+        v.grid[cur ^ (i & 1)], v.grid[cur ^ ((i + 1) & 1)], v.star_f, v.star_n, v.ncode, v.tab, v.nux, v.nuy,
+        tiles_x, it.y, v.dt_u, v.dt_over_tau_u, v.uw, k, v.n_sub, m0, min(kSubstepBlock, v.n_sub - m0), nullptr,
+        nullptr, nullptr, 0);
 }
 
 
@@ -1409,9 +1604,7 @@ template <class T, class R>
 hipError_t Kernels<T, R>::prepare() {
 #define HLBM_LDS(V)                                                                                                  \
   {reinterpret_cast<const void *>(&k_grid_substeps<R, V>), reinterpret_cast<const void *>(&kb_grid_substeps<T, R, V>), \
-   (int)substeps_lds_bytes<R, typename SubstepVariant<V>::G,                                                          \
-                           substeps_double_buffer<R, typename SubstepVariant<V>::G>()>(),                            \
-   (int)substeps_lds_bytes<R, typename SubstepVariant<V>::G>()}
+   (int)variant_lds_bytes<R, SubstepVariant<V>>(), (int)variant_lds_bytes<R, SubstepVariant<V>, true>()}
   struct FnLds {
     const void *f, *fb;
     int lds, lds_b;
@@ -1426,8 +1619,7 @@ hipError_t Kernels<T, R>::prepare() {
   }
 #define HLBM_LDS1(V)                                                                                      \
   {reinterpret_cast<const void *>(&k_grid_substeps<R, V>), nullptr,                                       \
-   (int)substeps_lds_bytes<R, typename SubstepVariant<V>::G,                                              \
-                           substeps_double_buffer<R, typename SubstepVariant<V>::G>()>(), 0}
+   (int)variant_lds_bytes<R, SubstepVariant<V>>(), 0}
   const FnLds single[] = {HLBM_LDS1(8), HLBM_LDS1(9), HLBM_LDS1(10)};
 #undef HLBM_LDS1
   for (const auto &e : single) {
@@ -1508,7 +1700,7 @@ void Kernels<T, R>::grid_substeps_v(const CaseView<T, R> &v, const R *f, R *fout
                                     hipEvent_t stop) {
   using SV = SubstepVariant<V>;
   const int tiles_x = (v.nux + SV::G::TX - 1) / SV::G::TX, tiles_y = (v.nuy + SV::G::TY - 1) / SV::G::TY;
-  constexpr size_t lds = substeps_lds_bytes<R, typename SV::G, substeps_double_buffer<R, typename SV::G>()>();
+  constexpr size_t lds = variant_lds_bytes<R, SV>();
   if (start || stop)
     hipExtLaunchKernelGGL((k_grid_substeps<R, V>), dim3(tiles_x * tiles_y), dim3(SV::NT), lds, s, start, stop, 0,
                           f, fout,
@@ -1610,7 +1802,7 @@ void Kernels<T, R>::batched(BatchKernel which, const CaseView<T, R> *views, cons
       switch (threads < 0 ? default_substep_variant<R>() : threads) {
 #define HLBM_KB(V)                                                                                                \
   hipLaunchKernelGGL((kb_grid_substeps<T, R, V>), g, dim3(SubstepVariant<V>::NT),                              \
-                     (substeps_lds_bytes<R, typename SubstepVariant<V>::G>()), s, views, items, m0)
+                     (variant_lds_bytes<R, SubstepVariant<V>, true>()), s, views, items, m0)
         case 1: HLBM_KB(1); break;
         case 2: HLBM_KB(2); break;
         case 3: HLBM_KB(3); break;
