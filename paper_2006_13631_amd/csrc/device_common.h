@@ -71,6 +71,23 @@ struct Stor<__half> {  // deviation from the rest equilibrium w_i
 __device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
+// c_q . (x, y): the components of c_q are 0 or +-1, so the sum needs no
+// product (a product with the constant 0 is not dropped by the compiler, for
+// it would not be 0 at an infinity). q must be a constant after unrolling.
+template <class R>
+__device__ __forceinline__ R cdot(int q, R x, R y) {
+  if (CXd[q] == 0) return CYd[q] == 0 ? R(0) : (CYd[q] > 0 ? y : -y);
+  const R sx = CXd[q] > 0 ? x : -x;
+  return CYd[q] == 0 ? sx : sx + (CYd[q] > 0 ? y : -y);
+}
+// c_q c_q : (xx, xy, yy), likewise
+template <class R>
+__device__ __forceinline__ R ccdot(int q, R xx, R xy, R yy) {
+  if (CXd[q] == 0) return CYd[q] == 0 ? R(0) : yy;
+  if (CYd[q] == 0) return xx;
+  return (xx + R(2 * CXd[q] * CYd[q]) * xy) + yy;
+}
+
 // ---- D2Q9 equilibrium and moments ------------------------------------------
 // Eq.(local_eq) with c_s^2 = 1/3: w rho (1 + 3 c.u + 9/2 (c.u)^2 - 3/2 u^2)
 template <class R>
@@ -78,8 +95,8 @@ __device__ __forceinline__ void equilibrium(R rho, R ux, R uy, R e[9]) {
   const R one_uu = fmad(R(-1.5), fmad(ux, ux, uy * uy), R(1));
 #pragma unroll
   for (int q = 0; q < 9; ++q) {
-    const R cu = R(CXd[q]) * ux + R(CYd[q]) * uy;  // c components are 0 or +-1: exact
-    e[q] = wgt<R>(q) * rho * fmad(R(4.5) * cu, cu, fmad(R(3), cu, one_uu));
+    const R cu = cdot<R>(q, ux, uy);
+    e[q] = wgt<R>(q) * rho * (q == 0 ? one_uu : fmad(R(4.5) * cu, cu, fmad(R(3), cu, one_uu)));
   }
 }
 

@@ -136,63 +136,159 @@ __global__ __launch_bounds__(256) void kb_stream_collide(const CaseView<T, R> *_
 // also get t_{k+1} in B, from
 // which the single-step kernel advances the band after the grid has written
 // its interpolation nodes.
-template <class T, class R>
 //
-// Tile order: with stagger >= 0 (and a tile count divisible by 8) the tiles
-// are dealt to the eight XCDs (which take workgroups in turn) in contiguous
-// runs of rows, so the rows a tile's ring shares with the tiles above and
-// below are fetched into that XCD's L2 once; each XCD starts its run
-// `stagger` tiles further along, so the eight XCDs do not stream from
-// addresses a power of two apart (which share HBM channels). ndon leading
-// workgroups compute the interface donors, as in k_stream_collide.
-__global__ __launch_bounds__(512) void k_stream_collide2(CaseView<T, R> v, int tiles_x, int stagger, int ndon) {
-  constexpr int TX = kTwoStepTX, TY = kTwoStepTY, NT = 512, LX = TX + 2, LY = TY + 2, LN = LX * LY;
-  constexpr int P1 = (LN + NT - 1) / NT;
-  static_assert(TX * TY == NT, "one output node per lane");
+// Two kinds of tiles: one clear of the lattice's edges, of the band and of
+// the node around it takes a path without any boundary, rectangle or band
+// test, its nine pulls being one 32-bit byte offset per node on nine uniform
+// bases (the general path's wrapped 64-bit addresses and its two integer
+// divisions per node made the kernel instruction-bound in FP32 and FP16);
+// the others follow pull_index and pull_source.
+template <class T, class R, int NT>
+struct TwoStepTile {
+  static constexpr int TX = kTwoStepTX, TY = kTwoStepTY, LX = TX + 2, LY = TY + 2, LN = LX * LY;
+  static constexpr int P1 = (LN + NT - 1) / NT;  // nodes of the tile and its ring per lane
+  static_assert(TX * TY <= NT, "at most one output node per lane");
+
+  // whether every node the tile and its ring pull from lies inside the
+  // lattice, at a byte offset of less than 2^32 in its plane
+  static __device__ __forceinline__ bool inner(const CaseView<T, R> &v, int tx0, int ty0) {
+    return tx0 >= 2 && ty0 >= 2 && tx0 + TX + 2 <= v.nx && ty0 + TY + 2 <= v.ny &&
+           v.plane * sizeof(T) < ((size_t)1 << 32);
+  }
+  // whether the tile holds nodes of the band or of the ring around it
+  static __device__ __forceinline__ bool meets_band(const CaseView<T, R> &v, int tx0, int ty0) {
+    return v.bx0 <= v.bx1 && tx0 <= v.bx1 + 1 && tx0 + TX > v.bx0 - 1 && ty0 <= v.by1 + 1 && ty0 + TY > v.by0 - 1;
+  }
+  // node of the tile and its ring that lane slot i takes, wrapped into the
+  // lattice (a ragged tile's overhang lands on other nodes and is not used)
+  static __device__ __forceinline__ void node(const CaseView<T, R> &v, int tx0, int ty0, int i, int &x, int &y) {
+    x = tx0 - 1 + i % LX;
+    y = ty0 - 1 + i / LX;
+    x += x < 0 ? v.nx : (x >= v.nx ? -v.nx : 0);
+    y += y < 0 ? v.ny : (y >= v.ny ? -v.ny : 0);
+  }
+  static __device__ __forceinline__ void load(const CaseView<T, R> &v, int tx0, int ty0, bool in, R f[P1][9]) {
+#pragma unroll
+    for (int u = 0; u < P1; ++u) {
+      const int i = threadIdx.x + u * NT;
+      if (i >= LN) continue;
+      if (in) {
+        const unsigned at = (unsigned)((ty0 - 1 + i / LX) * v.nx + (tx0 - 1 + i % LX)) * (unsigned)sizeof(T);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+          const char *base = (const char *)(v.A + ((ptrdiff_t)(q * v.plane) - (ptrdiff_t)(CYd[q] * v.nx + CXd[q])));
+          f[u][q] = Stor<T>::ld((const T *)(base + at), 0, q);
+        }
+      } else {
+        int x, y;
+        node(v, tx0, ty0, i, x, y);
+        pull<T, R>(v.A, v.nx, v.ny, v.plane, v.bc, x, y, f[u]);
+      }
+    }
+  }
+  static __device__ __forceinline__ void collide(const CaseView<T, R> &v, R f[9], R &rho) {
+    R e[9], ux, uy;
+    moments<R>(f, rho, ux, uy);
+    equilibrium<R>(rho, ux, uy, e);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) f[q] = fmad(-v.inv_tau, f[q] - e[q], f[q]);
+  }
+  // the first step, into LDS as the lattice would store it
+  static __device__ __forceinline__ void first(const CaseView<T, R> &v, R f[P1][9], R *s) {
+#pragma unroll
+    for (int u = 0; u < P1; ++u) {
+      const int i = threadIdx.x + u * NT;
+      if (i >= LN) continue;
+      R rho;
+      collide(v, f[u], rho);
+#pragma unroll
+      for (int q = 0; q < 9; ++q) s[q * LN + i] = f[u][q];
+    }
+  }
+  // the second step of every tile node outside the band, into C
+  static __device__ __forceinline__ void second(const CaseView<T, R> &v, int tx0, int ty0, bool in, bool band,
+                                                const R *s) {
+    const int ox = threadIdx.x % TX, oy = threadIdx.x / TX;
+    const int x = tx0 + ox, y = ty0 + oy;
+    if (oy >= TY || x >= v.nx || y >= v.ny) return;
+    if (band && x >= v.bx0 && x <= v.bx1 && y >= v.by0 && y <= v.by1) return;
+    const int l = (oy + 1) * LX + ox + 1;
+    R g[9], rho;
+    if (in) {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) g[q] = Stor<T>::round_trip(s[q * LN + l - CYd[q] * LX - CXd[q]], q);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) {
+        int qs, xs, ys;
+        pull_source(v.nx, v.ny, v.bc, x, y, q, qs, xs, ys);
+        int lx = xs - (tx0 - 1), ly = ys - (ty0 - 1);  // tile coordinates, across a periodic seam too
+        lx += lx < 0 ? v.nx : (lx >= LX ? -v.nx : 0);
+        ly += ly < 0 ? v.ny : (ly >= LY ? -v.ny : 0);
+        g[q] = Stor<T>::round_trip(s[qs * LN + ly * LX + lx], qs);  // as if stored at t_{k+1} and loaded
+      }
+    }
+    collide(v, g, rho);
+    check_density(v.flag, rho);
+    const size_t c = (size_t)y * v.nx + x;
+    if (in) {
+      const unsigned at = (unsigned)c * (unsigned)sizeof(T);
+#pragma unroll
+      for (int q = 0; q < 9; ++q) Stor<T>::st_stream((T *)((char *)(v.C + q * v.plane) + at), 0, q, g[q]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) Stor<T>::st_stream(v.C, q * v.plane + c, q, g[q]);
+    }
+  }
+};
+
+// Tile order: the tiles are listed in `order` (launch position to tile, -1:
+// none), or taken in turn. A launch over a list deals it to the eight XCDs
+// (which take workgroups in turn) in contiguous runs of rows, so the rows a
+// tile's ring shares with the tiles above and below are fetched into that
+// XCD's L2 once; each XCD starts its run three tile rows and five tiles
+// further along, so the eight XCDs do not stream from addresses a power of
+// two apart (which share HBM channels). ndon leading workgroups compute the
+// interface donors, as in k_stream_collide.
+template <class T, class R>
+__global__ __launch_bounds__(512) void k_stream_collide2(CaseView<T, R> v, int tiles_x,
+                                                         const int *__restrict__ order, int ndon) {
+  constexpr int NT = 512;
+  using Tile = TwoStepTile<T, R, NT>;
+  constexpr int TX = Tile::TX, LX = Tile::LX, LN = Tile::LN, P1 = Tile::P1;
   __shared__ R s[9 * LN];
-  const int nx = v.nx, ny = v.ny;
-  const size_t plane = v.plane;
   int t = (int)blockIdx.x - ndon;
   if (t < 0) {
     interface_donors_block<T, R>(v, v.A, *v.dk, blockIdx.x);
     return;
   }
-  const int ntiles = (int)gridDim.x - ndon;
-  if (stagger >= 0 && ntiles % 8 == 0) {
-    const int per = ntiles / 8, xcd = t % 8, i = t / 8;
-    t = xcd * per + (i + xcd * stagger) % per;
-  }
-  const int tx0 = (t % tiles_x) * TX, ty0 = (t / tiles_x) * TY;
+  if (order) t = order[t];
+  if (t < 0) return;
+  const int tx0 = (t % tiles_x) * TX, ty0 = (t / tiles_x) * Tile::TY;
+  const bool in = Tile::inner(v, tx0, ty0);
   R f[P1][9];
-  int node[P1];
-#pragma unroll
-  for (int u = 0; u < P1; ++u) {
-    const int i = threadIdx.x + u * NT;
-    if (i < LN) {
-      const int gx = ((tx0 - 1 + i % LX) % nx + nx) % nx, gy = ((ty0 - 1 + i / LX) % ny + ny) % ny;
-      node[u] = gy * nx + gx;
-      pull<T, R>(v.A, nx, ny, plane, v.bc, gx, gy, f[u]);
-    }
+  Tile::load(v, tx0, ty0, in, f);
+  if (!Tile::meets_band(v, tx0, ty0)) {
+    Tile::first(v, f, s);
+    __syncthreads();
+    Tile::second(v, tx0, ty0, in, false, s);
+    return;
   }
-  int ix0 = 1, ix1 = 0, iy0 = 1, iy1 = 0;
-  if (v.has_grid) {
-    const StepParams &P = v.params[*v.dkl];
-    ix0 = P.ix0, ix1 = P.ix1, iy0 = P.iy0, iy1 = P.iy1;
-  }
+  const size_t plane = v.plane;
+  const StepParams &P = v.params[*v.dkl];
+  const int ix0 = P.ix0, ix1 = P.ix1, iy0 = P.iy0, iy1 = P.iy1;
 #pragma unroll
   for (int u = 0; u < P1; ++u) {
     const int i = threadIdx.x + u * NT;
     if (i >= LN) continue;
-    const int gx = node[u] % nx, gy = node[u] / nx;
+    int gx, gy;
+    Tile::node(v, tx0, ty0, i, gx, gy);
+    R rho;
     if (gx >= ix0 && gx <= ix1 && gy >= iy0 && gy <= iy1) {
 #pragma unroll
-      for (int q = 0; q < 9; ++q) f[u][q] = Stor<T>::ld(v.A, q * plane + node[u], q);
+      for (int q = 0; q < 9; ++q) f[u][q] = Stor<T>::ld(v.A, q * plane + (size_t)gy * v.nx + gx, q);
     } else {
-      R e[9], rho, ux, uy;
-      moments<R>(f[u], rho, ux, uy);
-      equilibrium<R>(rho, ux, uy, e);
-#pragma unroll
-      for (int q = 0; q < 9; ++q) f[u][q] = fmad(-v.inv_tau, f[u][q] - e[q], f[u][q]);
+      Tile::collide(v, f[u], rho);
     }
 #pragma unroll
     for (int q = 0; q < 9; ++q) s[q * LN + i] = f[u][q];
@@ -200,10 +296,9 @@ __global__ __launch_bounds__(512) void k_stream_collide2(CaseView<T, R> v, int t
   __syncthreads();
   const int ox = threadIdx.x % TX, oy = threadIdx.x / TX;
   const int x = tx0 + ox, y = ty0 + oy;
-  if (x >= nx || y >= ny) return;
-  const size_t c = (size_t)y * nx + x;
-  const int l = (oy + 1) * LX + ox + 1;
-  if (x >= v.bx0 - 1 && x <= v.bx1 + 1 && y >= v.by0 - 1 && y <= v.by1 + 1) {
+  if (x < v.nx && y < v.ny && x >= v.bx0 - 1 && x <= v.bx1 + 1 && y >= v.by0 - 1 && y <= v.by1 + 1) {
+    const size_t c = (size_t)y * v.nx + x;
+    const int l = (oy + 1) * LX + ox + 1;
     if (x >= ix0 && x <= ix1 && y >= iy0 && y <= iy1) {
 #pragma unroll
       for (int q = 0; q < 9; ++q) v.B[q * plane + c] = v.A[q * plane + c];
@@ -211,24 +306,8 @@ __global__ __launch_bounds__(512) void k_stream_collide2(CaseView<T, R> v, int t
 #pragma unroll
       for (int q = 0; q < 9; ++q) Stor<T>::st_stream(v.B, q * plane + c, q, s[q * LN + l]);
     }
-    if (x >= v.bx0 && x <= v.bx1 && y >= v.by0 && y <= v.by1) return;
   }
-  R g[9];
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    int qs, xs, ys;
-    pull_source(nx, ny, v.bc, x, y, q, qs, xs, ys);
-    int lx = xs - (tx0 - 1), ly = ys - (ty0 - 1);  // tile coordinates, across a periodic seam too
-    lx += lx < 0 ? nx : (lx >= LX ? -nx : 0);
-    ly += ly < 0 ? ny : (ly >= LY ? -ny : 0);
-    g[q] = Stor<T>::round_trip(s[qs * LN + ly * LX + lx], qs);  // as if stored at t_{k+1} and loaded
-  }
-  R e[9], rho, ux, uy;
-  moments<R>(g, rho, ux, uy);
-  check_density(v.flag, rho);
-  equilibrium<R>(rho, ux, uy, e);
-#pragma unroll
-  for (int q = 0; q < 9; ++q) Stor<T>::st_stream(v.C, q * plane + c, q, fmad(-v.inv_tau, g[q] - e[q], g[q]));
+  Tile::second(v, tx0, ty0, in, true, s);
 }
 
 // ---- K2: lattice interpolation nodes from the grid, Eq.(postcollision2_s) ----
@@ -533,9 +612,9 @@ __device__ __forceinline__ void grid_substeps_block(
         if (CYd[q] != 0) ay = fmad(cl.Gy[s], fq, ay);
       }
       srho += a;
-      if (CXd[q] != 0) sjx += R(CXd[q]) * a;
-      if (CYd[q] != 0) sjy += R(CYd[q]) * a;
-      o9[q] = fmad(-dt_tau, a, fmad(dt, R(CXd[q]) * ax + R(CYd[q]) * ay, sl[row[SELF_SLOT] + q]));
+      if (CXd[q] != 0) sjx += CXd[q] > 0 ? a : -a;
+      if (CYd[q] != 0) sjy += CYd[q] > 0 ? a : -a;
+      o9[q] = fmad(-dt_tau, a, q == 0 ? sl[row[SELF_SLOT] + q] : fmad(dt, cdot<R>(q, ax, ay), sl[row[SELF_SLOT] + q]));
     }
     R pxx = R(0), pxy = R(0), pyy = R(0);
 #pragma unroll
@@ -549,10 +628,8 @@ __device__ __forceinline__ void grid_substeps_block(
     const R base = fmad(R(-1.5), pxx + pyy, srho);
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
-      const R cx = R(CXd[q]), cy = R(CYd[q]);
-      const R cu = cx * sjx + cy * sjy;
-      const R cc = (cx * cx) * pxx + (R(2) * cx * cy) * pxy + (cy * cy) * pyy;
-      o9[q] = fmad(dt_tau * wgt<R>(q), fmad(R(4.5), cc, fmad(R(3), cu, base)), o9[q]);
+      const R eq = q == 0 ? base : fmad(R(4.5), ccdot<R>(q, pxx, pxy, pyy), fmad(R(3), cdot<R>(q, sjx, sjy), base));
+      o9[q] = fmad(dt_tau * wgt<R>(q), eq, o9[q]);
     }
   };
   // copy a sub-step reads (offset into the LDS values); DB: the other copy
@@ -790,9 +867,9 @@ __device__ __forceinline__ void grid_fixed_block(
           if (CYd[q] != 0) ay = fmad(w[i][2], fq, ay);
         }
         srho += a;
-        if (CXd[q] != 0) sjx += R(CXd[q]) * a;
-        if (CYd[q] != 0) sjy += R(CYd[q]) * a;
-        res[q] = fmad(-dt_tau, a, fmad(dt, R(CXd[q]) * ax + R(CYd[q]) * ay, own[q]));
+        if (CXd[q] != 0) sjx += CXd[q] > 0 ? a : -a;
+        if (CYd[q] != 0) sjy += CYd[q] > 0 ? a : -a;
+        res[q] = fmad(-dt_tau, a, q == 0 ? own[q] : fmad(dt, cdot<R>(q, ax, ay), own[q]));
       }
       R pxx = R(0), pxy = R(0), pyy = R(0);
 #pragma unroll
@@ -804,10 +881,8 @@ __device__ __forceinline__ void grid_fixed_block(
       const R base = fmad(R(-1.5), pxx + pyy, srho);
 #pragma unroll
       for (int q = 0; q < 9; ++q) {
-        const R cx = R(CXd[q]), cy = R(CYd[q]);
-        const R cu = cx * sjx + cy * sjy;
-        const R cc = (cx * cx) * pxx + (R(2) * cx * cy) * pxy + (cy * cy) * pyy;
-        res[q] = fmad(dt_tau * wgt<R>(q), fmad(R(4.5), cc, fmad(R(3), cu, base)), res[q]);
+        const R eq = q == 0 ? base : fmad(R(4.5), ccdot<R>(q, pxx, pxy, pyy), fmad(R(3), cdot<R>(q, sjx, sjy), base));
+        res[q] = fmad(dt_tau * wgt<R>(q), eq, res[q]);
       }
       if (typ == NODE_WALL) {  // impose the lamina velocity, keep rho and f^neq
         R e[9], ew[9], r, vx, vy;
@@ -972,17 +1047,15 @@ __global__ __launch_bounds__(kMeshThreads) void k_mesh_substep(CaseView<T, R> v,
 #pragma unroll
   for (int q = 0; q < 9; ++q) {
     srho += a[q];
-    if (CXd[q] != 0) sjx += R(CXd[q]) * a[q];
-    if (CYd[q] != 0) sjy += R(CYd[q]) * a[q];
-    out[q] = fmad(-dt_tau, a[q], fmad(dt, R(CXd[q]) * ax[q] + R(CYd[q]) * ay[q], self[q]));
+    if (CXd[q] != 0) sjx += CXd[q] > 0 ? a[q] : -a[q];
+    if (CYd[q] != 0) sjy += CYd[q] > 0 ? a[q] : -a[q];
+    out[q] = fmad(-dt_tau, a[q], q == 0 ? self[q] : fmad(dt, cdot<R>(q, ax[q], ay[q]), self[q]));
   }
   const R base = fmad(R(-1.5), pxx + pyy, srho);
 #pragma unroll
   for (int q = 0; q < 9; ++q) {
-    const R cx = R(CXd[q]), cy = R(CYd[q]);
-    const R cu = cx * sjx + cy * sjy;
-    const R cc = (cx * cx) * pxx + (R(2) * cx * cy) * pxy + (cy * cy) * pyy;
-    out[q] = fmad(dt_tau * wgt<R>(q), fmad(R(4.5), cc, fmad(R(3), cu, base)), out[q]);
+    const R eq = q == 0 ? base : fmad(R(4.5), ccdot<R>(q, pxx, pxy, pyy), fmad(R(3), cdot<R>(q, sjx, sjy), base));
+    out[q] = fmad(dt_tau * wgt<R>(q), eq, out[q]);
   }
   if (typ == NODE_WALL) {  // impose the lamina velocity, keep rho and f^neq
     R e[9], ew[9], r, vx, vy;
@@ -1670,17 +1743,16 @@ void Kernels<T, R>::stream_collide(const CaseView<T, R> &v, hipStream_t s, hipEv
 
 template <class T, class R>
 void Kernels<T, R>::stream_collide2(const CaseView<T, R> &v, hipStream_t s, hipEvent_t start, hipEvent_t stop,
-                                    int order, bool donors) {
-  const int tiles_x = (int)blocks(v.nx, kTwoStepTX), tiles = tiles_x * (int)blocks(v.ny, kTwoStepTY);
-  // three tile rows and five tiles: measured on 2048^2 against other offsets
-  const int segments = order == 1 ? 3 * tiles_x + 5 : -1;
+                                    const int *order, int n, bool donors) {
+  const int tiles_x = (int)blocks(v.nx, kTwoStepTX);
+  if (!order) n = tiles_x * (int)blocks(v.ny, kTwoStepTY);
   constexpr int nt = kTwoStepTX * kTwoStepTY;
   const int ndon = donors && v.n_iface > 0 ? donor_groups(v.n_iface, nt) : 0;
   if (start || stop)
-    hipExtLaunchKernelGGL((k_stream_collide2<T, R>), dim3(tiles + ndon), dim3(nt), 0, s, start, stop, 0, v, tiles_x,
-                          segments, ndon);
-  else
-    hipLaunchKernelGGL((k_stream_collide2<T, R>), dim3(tiles + ndon), dim3(nt), 0, s, v, tiles_x, segments, ndon);
+    hipExtLaunchKernelGGL((k_stream_collide2<T, R>), dim3(n + ndon), dim3(nt), 0, s, start, stop, 0, v, tiles_x,
+                          order, ndon);
+  else if (n + ndon > 0)
+    hipLaunchKernelGGL((k_stream_collide2<T, R>), dim3(n + ndon), dim3(nt), 0, s, v, tiles_x, order, ndon);
 }
 
 template <class T, class R>
