@@ -365,6 +365,7 @@ class Case final : public CaseBase {
       for (int64_t k = 0; k <= cap; ++k)
         hmax = std::max(hmax, std::max(P[k].iy1, P[k].piy1) - std::min(P[k].iy0, P[k].piy0) + 1);
       k2_h_ = hmax;
+      if (!mesh) plan_refill();
       if (c.ckpt_every > 0) {
         // checkpoints of (lattice, grid) at every multiple of ckpt_every
         ckW_ = c.ckpt_every;
@@ -409,7 +410,9 @@ class Case final : public CaseBase {
     }
   }
 
-  hipError_t enqueue_step() {
+  // more: another step follows before anyone may read or replace the state
+  // (so this one's refill may also write the next one's interpolation nodes)
+  hipError_t enqueue_step(bool more = false) {
     hipError_t e = hipSuccess;
     CaseView<T, R> v = view();
     if (timing_ == 1) ENQ(hipEventRecord(tev_[tslot_][0], s_main_));
@@ -417,7 +420,7 @@ class Case final : public CaseBase {
       // 0. a bending grid takes the configuration of t_k
       if (deform_) Kernels<T, R>::mesh_deform(deform_view(), s_main_);
       // 1. lattice interpolation nodes from the grid at t_k, Eq.(postcollision2_s)
-      Kernels<T, R>::lattice_from_grid(v, (const R *)gbuf_[gcur_], s_main_);
+      from_grid(v);
       if (timing_ == 1) ENQ(hipEventRecord(tev_[tslot_][1], s_main_));
       if (s_grid_ != s_main_) {
         ENQ(hipEventRecord(ev_fork_, s_main_));
@@ -429,7 +432,7 @@ class Case final : public CaseBase {
       const bool fuse = s_grid_ == s_main_ && timing_ != 1;
       stream_collide_timed(v, fuse);
       // 3.-6. grid path: donors, n sub-steps, refill, force
-      ENQ(enqueue_grid_path(v, fuse));
+      ENQ(enqueue_grid_path(v, fuse, more ? v.B : nullptr));
       if (s_grid_ != s_main_) {
         ENQ(hipEventRecord(ev_join_, s_grid_));
         ENQ(hipStreamWaitEvent(s_main_, ev_join_, 0));
@@ -449,7 +452,9 @@ class Case final : public CaseBase {
   // Grid path of the step whose lattice (post-collision at t_k) v.A holds:
   // donors (unless the lattice launch computed them), n sub-steps, refill,
   // force (steps 3-6 of the step).
-  hipError_t enqueue_grid_path(const CaseView<T, R> &v, bool donors_done = false) {
+  // next: the lattice of t_{k+1}, complete when the refill runs, if the next
+  // step follows at once (null: it does not)
+  hipError_t enqueue_grid_path(const CaseView<T, R> &v, bool donors_done = false, T *next = nullptr) {
     hipError_t e = hipSuccess;
     if (timing_ == 1) ENQ(hipEventRecord(tev_[tslot_][3], s_grid_));
     if (!donors_done) Kernels<T, R>::interface_donors(v, s_grid_);
@@ -490,7 +495,10 @@ class Case final : public CaseBase {
       Kernels<T, R>::refill(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], s_grid_);
       Kernels<T, R>::advance_step(v, s_grid_);
     } else if (timing_ != 1) {  // one launch (level 1 times the two apart)
-      Kernels<T, R>::refill_force(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], done_, s_grid_);
+      if (!next_fits_ || s_grid_ != s_main_) next = nullptr;
+      Kernels<T, R>::refill_force(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], done_, outside_rows_, s_grid_, next,
+                                  next_targets_);
+      next_done_ = next != nullptr;
     } else {
       Kernels<T, R>::refill(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], s_grid_);
       if (timing_ == 1) ENQ(hipEventRecord(tev_[tslot_][5], s_grid_));
@@ -501,13 +509,20 @@ class Case final : public CaseBase {
     return e;
   }
 
+  // lattice interpolation nodes of the step, unless the previous step's
+  // refill wrote them
+  void from_grid(const CaseView<T, R> &v) {
+    if (!next_done_) Kernels<T, R>::lattice_from_grid(v, (const R *)gbuf_[gcur_], s_main_);
+    next_done_ = false;
+  }
+
   // Two structured steps t_k -> t_{k+2}. Outside the band the lattice takes
   // both steps in one launch (A -> C); the band takes the first step there
   // too (into B), and after step k's grid path and step k+1's interpolation
   // nodes, its second step with the single-step kernel (B -> C, on the band
   // only). Every node computes what two single steps compute, in the same
   // arithmetic. Afterwards C holds t_{k+2}.
-  hipError_t enqueue_pair() {
+  hipError_t enqueue_pair(bool more = false) {
     hipError_t e = hipSuccess;
     CaseView<T, R> v = view();
     const bool two = s_grid_ != s_main_;  // the grid path on its own stream
@@ -521,7 +536,7 @@ class Case final : public CaseBase {
     };
     if (has_grid_) {
       if (deform_) Kernels<T, R>::mesh_deform(deform_view(), s_main_);
-      Kernels<T, R>::lattice_from_grid(v, (const R *)gbuf_[gcur_], s_main_);
+      from_grid(v);
     }
     // step k's grid path reads only the lattice of t_k: it may run beside
     // the two-step launch, which then reads a copy of the step counter (the
@@ -540,7 +555,7 @@ class Case final : public CaseBase {
     else
       Kernels<T, R>::stream_collide2(v, s_main_, nullptr, nullptr, tile_list(two_step_order_), n_tiles_, fuse);
     if (has_grid_) {
-      ENQ(enqueue_grid_path(v, fuse));
+      ENQ(enqueue_grid_path(v, fuse, v.B));
       if (two) ENQ(join());
       CaseView<T, R> w = view();
       w.A = (const T *)lat_[1];
@@ -551,11 +566,11 @@ class Case final : public CaseBase {
       w.wh = band_[3] - band_[2] + 1;
       // (step k's refill and force have read the configuration of t_k)
       if (deform_) Kernels<T, R>::mesh_deform(deform_view(), s_main_);
-      Kernels<T, R>::lattice_from_grid(w, (const R *)gbuf_[gcur_], s_main_);
+      from_grid(w);
       // step k+1's grid path and the band's second step both read t_{k+1}
       if (two) ENQ(fork());
       Kernels<T, R>::stream_collide(w, s_main_, nullptr, nullptr, lattice_threads_, lattice_rows_, 0, fuse);
-      ENQ(enqueue_grid_path(w, fuse));
+      ENQ(enqueue_grid_path(w, fuse, more ? w.B : nullptr));
       if (two) ENQ(join());
     }
     if (timing_) ++tslot_;
@@ -575,10 +590,10 @@ class Case final : public CaseBase {
     while (*done < n) {
       hipError_t e;
       if (two_step_ && timing_ != 1 && n - *done >= 2) {
-        e = enqueue_pair();
+        e = enqueue_pair(*done + 2 < n);
         if (e == hipSuccess) *done += 2;
       } else {
-        e = enqueue_step();
+        e = enqueue_step(*done + 1 < n);
         if (e == hipSuccess) *done += 1;
       }
       if (e != hipSuccess) return e;
@@ -1492,6 +1507,41 @@ class Case final : public CaseBase {
     return true;
   }
 
+  // Sizes of the refill launch: the rows at either end of the grid that a
+  // step's motion may take out of its old extent, the largest number of
+  // lattice interpolation nodes of a step (the rectangle's perimeter and the
+  // rows it uncovered), and whether the refill may write those of the next
+  // step: every node of a triangle that can hold one (2 or more inside the
+  // grid's edge) must lie farther from the edge than a step moves.
+  void plan_refill() {
+    double dmax = 0.0;
+    next_targets_ = 0;
+    for (const StepParams &S : P_host_) {
+      dmax = std::max(dmax, std::fabs(S.y1 - S.y));
+      const int w = std::max(0, S.ix1 - S.ix0 + 1), hh = std::max(0, S.iy1 - S.iy0 + 1);
+      const int rows = std::max(0, std::min(S.piy1, S.iy0 - 1) - S.piy0 + 1) +
+                       std::max(0, S.piy1 - std::max(S.piy0, S.iy1 + 1) + 1);
+      next_targets_ = std::max(next_targets_, 2 * (w + hh) + std::max(0, S.pix1 - S.pix0 + 1) * rows);
+    }
+    dmax += 1e-6;
+    const int ny = cfg_.nuy;
+    // distance of row j from the edge it is nearer to in the order from
+    // below (up = 0) or above (up = 1)
+    auto dist = [&](int j, int up) {
+      const double y = gy_.empty() ? (double)j * h_ : gy_[up ? ny - 1 - j : j] - (up ? gy_[ny - 1] : gy_[0]);
+      return std::fabs(y);
+    };
+    outside_rows_ = 0;
+    next_fits_ = true;
+    for (int up = 0; up < 2; ++up) {
+      int r = 0;
+      while (r < ny / 2 && dist(r, up) < dmax) ++r;
+      outside_rows_ = std::max(outside_rows_, r);
+      for (int j = 0; j + 1 < ny; ++j)
+        if (dist(j + 1, up) > kMargin - 1e-6 && dist(j, up) < dmax) next_fits_ = false;
+    }
+  }
+
   // Launch positions of the two-step tiles in contiguous runs per XCD, each
   // run starting three tile rows and five tiles further along (measured on
   // 2048^2 against other offsets); a count not divisible by 8 stays in turn.
@@ -1645,7 +1695,7 @@ class Case final : public CaseBase {
   void *lattice_buffer(int i) const { return lat_[i]; }  // 0: state at t_k, 1: at t_{k-1}
   size_t plane() const { return plane_; }
   bool has_grid() const { return has_grid_; }
-  hipError_t enqueue_one() { return enqueue_step(); }
+  hipError_t enqueue_one(bool more) { return enqueue_step(more); }
   struct Layout {
     void *l0, *l1, *l2;
     int gcur;
@@ -2045,6 +2095,10 @@ class Case final : public CaseBase {
   int sub_n_[kTimingRing] = {};
   int tslot_ = 0;
   int timing_ = 0;  // 1: every kernel, 2: the stream-collide only
+  int outside_rows_ = 0;    // grid rows at either end a step may move out of the old grid
+  bool next_fits_ = false;  // the refill may write the next step's interpolation nodes
+  int next_targets_ = 0;    // most lattice interpolation nodes of any step
+  bool next_done_ = false;  // the next step's are written already (never between calls)
   int *tiles_dealt_ = nullptr;  // two-step tiles, dealt to the XCDs in runs
   int n_tiles_ = 0;
   int substep_variant_ = -1;  // grid sub-step kernel variant (-1: the default for R)
@@ -2949,9 +3003,10 @@ class MultiLevel final : public CaseBase {
     }
   }
 
-  // enqueue one step of level l (and 2^(l'-l) of every finer level l')
-  hipError_t advance(int l) {
-    if (l == L_ - 1) return fine_->enqueue_one();
+  // enqueue one step of level l (and 2^(l'-l) of every finer level l');
+  // more: further steps of the finest level follow in the same run
+  hipError_t advance(int l, bool more = false) {
+    if (l == L_ - 1) return fine_->enqueue_one(more);
     Level &c = lev_[l];
     Kernels<T, R>::stream_collide(level_view(l), s_, nullptr, nullptr, threads_, rows_, order_);
     std::swap(c.lat[0], c.lat[1]);
@@ -2968,7 +3023,7 @@ class MultiLevel final : public CaseBase {
       child(l + 1, &fc, &fp, &nxf, &nyf, &planef, &tauf);
       LevelKernels<T, R>::prolong((const R *)c.m[0], (const R *)c.m[1], c.box, 0.5 * (double)h, kf, (T *)fc, nxf, nyf,
                                   planef, s_);
-      const hipError_t e = advance(l + 1);
+      const hipError_t e = advance(l + 1, more || h == 0);
       if (e != hipSuccess) return e;
     }
     child(l + 1, &fc, &fp, &nxf, &nyf, &planef, &tauf);

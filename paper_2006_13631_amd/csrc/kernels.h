@@ -204,8 +204,15 @@ struct Kernels {
   // *to = *from (one lane): a copy of the step counter
   static void copy_step(const int64_t *from, int64_t *to, hipStream_t s);
   // refill and force (prescribed motion) in one launch, then the step
-  // counter advances; done: a device counter that starts at 0 and is left at 0
-  static void refill_force(const CaseView<T, R> &v, const R *fold, R *fnew, unsigned *done, hipStream_t s);
+  // counter advances; done: a device counter that starts at 0 and is left at
+  // 0; outside_rows: grid rows at either end whose nodes the motion may take
+  // out of the old grid (split-quad grids); next (optional, split-quad
+  // grids): the lattice of t_{k+1}, complete and read by no one else during
+  // the launch, which also gets the interpolation nodes of step k + 1 (at
+  // most `targets` of them), as lattice_from_grid would write them from the
+  // refilled grid; no corner of their triangles may move out of the old grid
+  static void refill_force(const CaseView<T, R> &v, const R *fold, R *fnew, unsigned *done, int outside_rows,
+                           hipStream_t s, T *next = nullptr, int targets = 0);
   // advance = 0: leave the step counter (a coupled-motion step then runs the
   // refill and advance_step after it)
   static void force(const CaseView<T, R> &v, const R *f, hipStream_t s, int advance = 1);

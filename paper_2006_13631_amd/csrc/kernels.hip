@@ -1192,7 +1192,8 @@ __global__ __launch_bounds__(kDeformThreads) void k_mesh_deform(MeshDeformView<R
 // old lamina -> type 2 (keep f); otherwise -> type 1 (bilinear lattice
 // donors, f^neq,u = (1 - 1/(2 tau_s)) f^neq,s, Eq.(continuity_stresses)).
 // Wall nodes keep f (their velocity is imposed during the sub-steps).
-template <class T, class R>
+// INSIDE: type 1 nodes are left to outside_block.
+template <class T, class R, bool INSIDE = false>
 __device__ __forceinline__ void refill_block(const CaseView<T, R> &v, const T *__restrict__ A,
                                              const R *__restrict__ fo, R *__restrict__ fn, int64_t k, int bx) {
   const int p = bx * blockDim.x + threadIdx.x;
@@ -1243,6 +1244,8 @@ __device__ __forceinline__ void refill_block(const CaseView<T, R> &v, const T *_
 #pragma unroll
     for (int q = 0; q < 9; ++q) out[q] = fo[q * N + p];
     atomicAdd(&v.counts[1], 1ull);
+  } else if (INSIDE) {
+    return;
   } else {
     R rho, ux, uy, fneq[9], e[9];
     lattice_bilinear<T, R>(A, v.nx, v.ny, v.plane, v.bc, X, Ynew, rho, ux, uy, fneq);
@@ -1258,6 +1261,145 @@ __device__ __forceinline__ void refill_block(const CaseView<T, R> &v, const T *_
     rho += out[q];
   }
   check_density(v.flag, rho);
+}
+
+// The type 1 nodes of a split-quad grid: a node the grid moves out of its old
+// extent, so one of the n1 lowest or highest rows. Four consecutive lanes
+// take the four bilinear donors of one node (one round trip of loads in
+// place of four) and each sums them in the order of lattice_bilinear.
+template <class T, class R>
+__device__ __forceinline__ void outside_block(const CaseView<T, R> &v, const T *__restrict__ A, R *__restrict__ fn,
+                                              int64_t k, int n1, int bx) {
+  const int gt = bx * blockDim.x + threadIdx.x, t = gt >> 2, d = gt & 3;
+  const int i = t % v.nux, r = t / v.nux, j = r < n1 ? r : v.nuy - 2 * n1 + r, p = j * v.nux + i;
+  const StepParams &P = v.params[k];
+  bool valid = r < 2 * n1 && (v.ncode[p] & 3) != NODE_WALL;
+  R acc[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = R(0);
+  if (valid) {
+    const GridGeom gg{v.nux, v.nuy, v.h, v.xc, v.half_b, v.half_T, v.body, v.gx, v.gy};
+    valid = refill_cell(gg, P.ybase, P.ybase1, i, j).kind == 1;
+  }
+  if (valid) {
+    const double X = v.gx ? v.xc + v.gx[i] : v.xc + (double)(i - v.nux / 2) * v.h;
+    const double Ynew = v.gy ? P.ybase1 + v.gy[j] : P.ybase1 + ((double)j - 0.5 * (double)(v.nuy - 1)) * v.h;
+    donor_corner<T, R>(A, v.nx, v.ny, v.plane, v.bc, X, Ynew, d, acc);
+  }
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    const int l = threadIdx.x & 60;
+    const R a0 = __shfl(acc[c], l, 64), a1 = __shfl(acc[c], l + 1, 64), a2 = __shfl(acc[c], l + 2, 64),
+            a3 = __shfl(acc[c], l + 3, 64);
+    acc[c] = ((a0 + a1) + a2) + a3;
+  }
+  if (!valid) return;
+  R e[9], rho = R(0);
+  equilibrium<R>(acc[0], acc[1], acc[2], e);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const R out = e[q] + v.k_neq * acc[3 + q];
+    if ((q & 3) == d) fn[(size_t)q * v.nnode + p] = out;
+    rho += out;
+  }
+  if (d != 0) return;
+  atomicAdd(&v.counts[0], 1ull);
+  check_density(v.flag, rho);
+}
+
+// The refilled populations of a non-wall node the grid does not move out of
+// its old extent (types 3 and 2), as refill_block writes them.
+template <class T, class R>
+__device__ __forceinline__ void refill_inside(const CaseView<T, R> &v, const R *__restrict__ fo,
+                                              const StepParams &P, int p, R out[9]) {
+  const size_t N = (size_t)v.nnode;
+  const GridGeom gg{v.nux, v.nuy, v.h, v.xc, v.half_b, v.half_T, v.body, v.gx, v.gy};
+  const RefillCell rc = refill_cell(gg, P.ybase, P.ybase1, p % v.nux, p / v.nux);
+  int node[3] = {p, p, p};
+  double lam[3], dlam[3];
+  if (rc.kind == 3) cell_triangle(rc.ci, rc.cj, v.nux, rc.a, rc.b, node, lam, dlam, rc.tri);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const R f0 = fo[q * N + node[0]];
+    out[q] = rc.kind == 3 ? R(lam[0]) * f0 + R(lam[1]) * fo[q * N + node[1]] + R(lam[2]) * fo[q * N + node[2]] : f0;
+  }
+}
+
+// Lattice interpolation nodes of step k + 1 (Eq.(postcollision2_s)) inside
+// the refill launch of step k, into the lattice of t_{k+1}: four lanes per
+// node, three of which refill one corner of its triangle for themselves (the
+// refill launch writes the same values, but not before this one may read
+// them), then the first lane interpolates them in the order of the kernel of
+// its own (grid_barycentric), so both give the same bits. The targets are
+// numbered along the rectangle's perimeter, then over the rows it uncovers.
+// The lattice of t_{k+1} is complete by then and no other workgroup of the
+// launch reads it. Split-quad grids with prescribed motion whose corners here
+// never move out of the old grid (the caller checks that).
+template <class T, class R>
+__device__ __forceinline__ void next_from_grid_block(const CaseView<T, R> &v, T *__restrict__ next,
+                                                     const R *__restrict__ fo, int64_t k, int bx) {
+  const int gt = bx * blockDim.x + threadIdx.x, i = gt >> 2, a = gt & 3;
+  const StepParams &P = v.params[k], &Q = v.params[k + 1];
+  const int W = Q.ix1 - Q.ix0 + 1, Hh = Q.iy1 - Q.iy0 + 1;
+  const int per = W < 1 || Hh < 1 ? 0 : (Hh == 1 ? W : 2 * W) + (W == 1 ? 1 : 2) * max(Hh - 2, 0);
+  int x, y;
+  if (i < per) {
+    const int rows = Hh == 1 ? W : 2 * W;
+    if (i < rows) {
+      x = Q.ix0 + i % W;
+      y = i < W ? Q.iy0 : Q.iy1;
+    } else {
+      const int r = i - rows, h = Hh - 2;
+      x = r < h ? Q.ix0 : Q.ix1;
+      y = Q.iy0 + 1 + r % h;
+    }
+  } else {
+    const int Wp = max(Q.pix1 - Q.pix0 + 1, 1), r = (i - per) / Wp;
+    const int lo = max(0, min(Q.piy1, Q.iy0 - 1) - Q.piy0 + 1);
+    x = Q.pix0 + (i - per) % Wp;
+    y = r < lo ? Q.piy0 + r : max(Q.piy0, Q.iy1 + 1) + (r - lo);
+  }
+  const bool valid = from_grid_target(Q, x, y);
+  R f[9], e[9], r = R(0), vx = R(0), vy = R(0);
+  double lam[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 9; ++q) f[q] = e[q] = R(0);
+  if (valid) {
+    const GridGeom gg{v.nux, v.nuy, v.h, v.xc, v.half_b, v.half_T, v.body, v.gx, v.gy};
+    int node[3], ci, cj, tri;
+    double ca, cb, dlam[3];
+    lattice_node_cell(gg, Q.ybase, x, y, ci, cj, ca, cb, tri);
+    cell_triangle(ci, cj, v.nux, ca, cb, node, lam, dlam, tri);
+    if (a < 3) {
+      const int p = a == 0 ? node[0] : a == 1 ? node[1] : node[2];
+      if ((v.ncode[p] & 3) == NODE_WALL) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) f[q] = fo[(size_t)q * v.nnode + p];
+      } else {
+        refill_inside<T, R>(v, fo, P, p, f);
+      }
+      moments<R>(f, r, vx, vy);
+      equilibrium<R>(r, vx, vy, e);
+    }
+  }
+  R rho = R(0), ux = R(0), uy = R(0), fneq[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) fneq[q] = R(0);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {  // corner c from lane c of the four
+    const int src = (threadIdx.x & 60) + c;
+    const R l = R(lam[c]);
+    rho += l * __shfl(r, src, 64);
+    ux += l * __shfl(vx, src, 64);
+    uy += l * __shfl(vy, src, 64);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) fneq[q] += l * (__shfl(f[q], src, 64) - __shfl(e[q], src, 64));
+  }
+  if (!valid || a != 0) return;
+  equilibrium<R>(rho, ux, uy, e);
+  const size_t c = (size_t)y * v.nx + x;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) Stor<T>::st(next, q * v.plane + c, q, e[q] + v.g_post * fneq[q]);
 }
 
 template <class T, class R>
@@ -1293,30 +1435,43 @@ __device__ __forceinline__ void force_block(const R *__restrict__ f, const WallE
   const int lane = threadIdx.x & 63;
   for (int vw = threadIdx.x >> 6; vw < kForceLanes / 64; vw += blockDim.x >> 6) {
     double Fx = 0.0, Fy = 0.0;
-    for (int e = vw * 64 + lane; e < n_wall_edges; e += kForceLanes) {
-      const WallEdge w = wall[e];
-      double tx = 0.0, ty = 0.0;
-      for (int s = 0; s < 2; ++s) {
-        const int p = s ? w.b : w.a;
-        R fp[9], eq[9], r, vx, vy;
+    // the lane's edges in pairs, the four ends' populations read together
+    for (int e0 = vw * 64 + lane; e0 < n_wall_edges; e0 += 2 * kForceLanes) {
+      const int n = e0 + kForceLanes < n_wall_edges ? 2 : 1;
+      WallEdge w[2];
+      R fp[2][2][9];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) fp[q] = f[(size_t)q * nnode + p];
-        moments<R>(fp, r, vx, vy);
-        equilibrium<R>(r, vx, vy, eq);
-        double sxx = 0.0, sxy = 0.0, syy = 0.0;
+      for (int i = 0; i < 2; ++i) w[i] = wall[i < n ? e0 + i * kForceLanes : e0];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) {
-          const double fn = (double)fp[q] - (double)eq[q];
-          sxx -= double(CXd[q] * CXd[q]) * fn;
-          sxy -= double(CXd[q] * CYd[q]) * fn;
-          syy -= double(CYd[q] * CYd[q]) * fn;
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int q = 0; q < 9; ++q) fp[i][s][q] = f[(size_t)q * nnode + (s ? w[i].b : w[i].a)];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (i >= n) break;
+        double tx = 0.0, ty = 0.0;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          R eq[9], r, vx, vy;
+          moments<R>(fp[i][s], r, vx, vy);
+          equilibrium<R>(r, vx, vy, eq);
+          double sxx = 0.0, sxy = 0.0, syy = 0.0;
+#pragma unroll
+          for (int q = 0; q < 9; ++q) {
+            const double fn = (double)fp[i][s][q] - (double)eq[q];
+            if (CXd[q] != 0) sxx -= fn;
+            if (CXd[q] * CYd[q] != 0) sxy -= CXd[q] * CYd[q] > 0 ? fn : -fn;
+            if (CYd[q] != 0) syy -= fn;
+          }
+          const double pp = ((double)r - 1.0) / 3.0;
+          tx += -pp * w[i].nx + sxx * w[i].nx + sxy * w[i].ny;
+          ty += -pp * w[i].ny + sxy * w[i].nx + syy * w[i].ny;
         }
-        const double pp = ((double)r - 1.0) / 3.0;
-        tx += -pp * w.nx + sxx * w.nx + sxy * w.ny;
-        ty += -pp * w.ny + sxy * w.nx + syy * w.ny;
+        Fx += 0.5 * w[i].len * tx;
+        Fy += 0.5 * w[i].len * ty;
       }
-      Fx += 0.5 * w.len * tx;
-      Fy += 0.5 * w.len * ty;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -1393,25 +1548,41 @@ __global__ __launch_bounds__(256) void k_force(const R *__restrict__ f, const Wa
 }
 
 // Refill and force of one case in one launch: workgroup 0 computes the
-// force of t_{k+1} on the grid before the refill, the others refill it.
-// Every workgroup reads the step counter first and counts itself done at
-// its end; the last one advances the counter (and clears the count for the
-// next launch), so no workgroup can read the advanced step.
-template <class T, class R>
-__global__ __launch_bounds__(256) void k_refill_force(CaseView<T, R> v, const R *__restrict__ fo,
-                                                      R *__restrict__ fn, unsigned *done) {
-  __shared__ int64_t k_s;
-  if (threadIdx.x == 0) k_s = *v.dk;
-  __syncthreads();
-  const int64_t k = k_s;
-  if (blockIdx.x == 0)
+// force of t_{k+1} on the grid before the refill; the next ones, on a
+// split-quad grid, its type 1 nodes; then (if the next step follows in the
+// same run) those that write that step's lattice interpolation nodes into
+// `next`, a launch of its own otherwise; the others refill the grid. The
+// long dependency chains come first. The launch is bound by those chains
+// (counter, parameters, node, its three corners): 9.7 us on the 512 x 128
+// grid in FP64 and 5.8 for the interpolation nodes' own launch, 13.0
+// together; on 64 x 32 nodes 6.7 and 5.0, 8.5 together; on 1024 x 256 20.3
+// and 8.5, 20.5 together. The grid's form (0 uniform, 1 graded, 2 any
+// triangulation) is a template argument: a kernel holding all three took
+// 14.5 us. Every workgroup reads the step
+// counter before it counts itself done; the last one advances the counter
+// (and clears the count for the next launch), so no workgroup can read the
+// advanced step.
+template <class T, class R, int GRID>
+__global__ __launch_bounds__(256) void k_refill_force(CaseView<T, R> vv, const R *__restrict__ fo,
+                                                      R *__restrict__ fn, unsigned *done, int n1, int nout,
+                                                      T *__restrict__ next, int nnext) {
+  CaseView<T, R> v = vv;
+  if (GRID == 0) v.gx = v.gy = nullptr;
+  v.mesh = GRID == 2;
+  const int64_t k = *v.dk;
+  const int b = (int)blockIdx.x - 1;
+  if (b < 0)
     force_block<R>(fo, v.wall, v.n_wall_edges, v.nnode, v.dk, v.hist, v.flag, MotionCtx{}, nullptr, nullptr, 0,
                    0);
+  else if (GRID != 2 && b < nout)
+    outside_block<T, R>(v, v.A, fn, k, n1, b);
+  else if (GRID != 2 && b < nout + nnext)
+    next_from_grid_block<T, R>(v, next, fo, k, b - nout);
   else
-    refill_block<T, R>(v, v.A, fo, fn, k, blockIdx.x - 1);
+    refill_block<T, R, GRID != 2>(v, v.A, fo, fn, k, b - nout - nnext);
   __syncthreads();
-  // the counter was read (into k) before this point; the next launch sees
-  // the advanced counter and the cleared count at the kernel boundary
+  // every lane of the workgroup has used k by now; the next launch sees the
+  // advanced counter and the cleared count at the kernel boundary
   if (threadIdx.x == 0) {
     if (atomicAdd(done, 1u) == gridDim.x - 1) {
       *done = 0u;
@@ -1817,8 +1988,17 @@ void Kernels<T, R>::force(const CaseView<T, R> &v, const R *f, hipStream_t s, in
 }
 
 template <class T, class R>
-void Kernels<T, R>::refill_force(const CaseView<T, R> &v, const R *fold, R *fnew, unsigned *done, hipStream_t s) {
-  hipLaunchKernelGGL((k_refill_force<T, R>), dim3(1 + blocks(v.nnode, 256)), dim3(256), 0, s, v, fold, fnew, done);
+void Kernels<T, R>::refill_force(const CaseView<T, R> &v, const R *fold, R *fnew, unsigned *done, int outside_rows,
+                                 hipStream_t s, T *next, int targets) {
+  const int nref = (int)blocks(v.nnode, 256), nnext = next ? (int)blocks((size_t)4 * targets, 256) : 0;
+  const int nout = v.mesh ? 0 : (int)blocks((size_t)8 * outside_rows * v.nux, 256);
+  const dim3 g(1 + nout + nnext + nref);
+#define HLBM_RF(GRID) \
+  hipLaunchKernelGGL((k_refill_force<T, R, GRID>), g, dim3(256), 0, s, v, fold, fnew, done, outside_rows, nout, next, nnext)
+  if (v.mesh) HLBM_RF(2);
+  else if (v.gx) HLBM_RF(1);
+  else HLBM_RF(0);
+#undef HLBM_RF
 }
 
 template <class T, class R>
