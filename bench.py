@@ -63,9 +63,9 @@ def measured_traffic(workload, storage, kernel="k_stream_collide"):
 
 
 def substeps_per_launch(variant, n_sub):
-    """Mean grid sub-steps per launch of a step: variants 8 and 9 advance
-    one per launch, 10 two, the others up to four."""
-    blk = {8: 1, 9: 1, 10: 2}.get(variant, 4)
+    """Mean grid sub-steps per launch of a step: variant 8 advances one per
+    launch, 10 two, the others up to four."""
+    blk = {8: 1, 10: 2}.get(variant, 4)
     return n_sub / -(-n_sub // blk)
 
 

@@ -139,15 +139,15 @@ typedef struct hlbm_tuning {
   int32_t lattice_rows;    /* lattice rows per lane of the stream-collide:
                               1, 2 or 4                                    */
   int32_t substep_variant; /* grid sub-step kernel (grid nodes per tile,
-                              workgroup size): -1 default (FP64 1, else
-                              3); 0: 16x16, 576; 1: 32x8, 640; 2: 64x4,
-                              896; 3: 16x8, 384; 4: 8x8, 64; 5: 16x8,
-                              128; 6: 16x16, 256; 7: 8x4, 64 (4-7: several
-                              nodes per lane, more workgroups per CU),
-                              each up to 4 sub-steps per launch; single
-                              case only: 8: 32x8, 256 and 9: 16x16, 256,
-                              one sub-step per launch; 10: 32x8, 384, two
-                              (large grids)                                */
+                              workgroup size): -1 default (single case: by
+                              the grid's size and precision; batch: 3);
+                              0: 32x16, 960; 1: 32x8, 640;
+                              2: 8x8, 256; 3: 24x16, 768; 4: 8x8, 64;
+                              5: 16x8, 128; 6: 16x16, 256; 7: 8x4, 64
+                              (4-7: several nodes per lane, more workgroups
+                              per CU), each up to 4 sub-steps per launch;
+                              single case only: 8: 32x8, 384, one sub-step
+                              per launch; 9: 24x8, 512; 10: 32x8, 448, two */
   int32_t order;           /* batch work lists: 0 case by case, 1 dealt to
                               the 8 XCDs in contiguous chunks; single
                               case: bit 0 gives each XCD a contiguous band

@@ -1260,7 +1260,7 @@ class Case final : public CaseBase {
       });
     } else if (has_grid_) {
       best_ms = 3e38f;
-      int best = default_substep_variant<R>();
+      int best = 0;
       for (int sv = 0; sv < kSubstepVariantsSingle; ++sv) {
         const int blk = substep_block(sv);
         const float ms = timed(s_grid_, [&] {
@@ -1514,16 +1514,10 @@ class Case final : public CaseBase {
   // step: every node of a triangle that can hold one (2 or more inside the
   // grid's edge) must lie farther from the edge than a step moves.
   void plan_refill() {
-    double dmax = 0.0;
-    next_targets_ = 0;
-    for (const StepParams &S : P_host_) {
-      dmax = std::max(dmax, std::fabs(S.y1 - S.y));
-      const int w = std::max(0, S.ix1 - S.ix0 + 1), hh = std::max(0, S.iy1 - S.iy0 + 1);
-      const int rows = std::max(0, std::min(S.piy1, S.iy0 - 1) - S.piy0 + 1) +
-                       std::max(0, S.piy1 - std::max(S.piy0, S.iy1 + 1) + 1);
-      next_targets_ = std::max(next_targets_, 2 * (w + hh) + std::max(0, S.pix1 - S.pix0 + 1) * rows);
-    }
-    dmax += 1e-6;
+    const double dmax = std::fabs(d_.A * d_.omega) + 1e-6;  // no step moves farther than the greatest speed
+    const StepParams &S = P_host_[0];
+    const int w = std::max(0, S.ix1 - S.ix0 + 1), hh = std::max(0, S.iy1 - S.iy0 + 2);
+    next_targets_ = 2 * (w + hh) + w * ((int)std::ceil(dmax) + 1);
     const int ny = cfg_.nuy;
     // distance of row j from the edge it is nearer to in the order from
     // below (up = 0) or above (up = 1)
@@ -2386,7 +2380,7 @@ class Batch final : public CaseBase {
         }
     const hlbm_tuning after_l = best;
     for (int sv = 0; sv < kSubstepVariants; ++sv)
-      if (sv != (after_l.substep_variant < 0 ? default_substep_variant<R>() : after_l.substep_variant)) {
+      if (sv != (after_l.substep_variant < 0 ? kBatchSubstepVariant : after_l.substep_variant)) {
         hlbm_tuning c = cand(after_l);
         c.substep_variant = sv;
         trial(c);
@@ -2535,7 +2529,7 @@ class Batch final : public CaseBase {
   // the sub-step kernel for this set of running cases
   int variant_for(const std::vector<int> &act) const {
     const int sv = (tuning_.tail_variant >= 0 && is_tail(act)) ? tuning_.tail_variant : tuning_.substep_variant;
-    return sv < 0 ? default_substep_variant<R>() : sv;
+    return sv < 0 ? kBatchSubstepVariant : sv;
   }
 
   bool persistent_for(const std::vector<int> &act) const {

@@ -137,25 +137,27 @@ constexpr int kTwoStepTX = 64, kTwoStepTY = 8;
 
 // Variants of the grid sub-step kernel (tile of grid nodes per workgroup,
 // workgroup size):
-//   0: 16 x 16, 576 threads   1: 32 x 8, 640 threads
-//   2: 64 x 4, 896 threads    3: 16 x 8, 384 threads
+//   0: 32 x 16, 960 threads   1: 32 x 8, 640 threads
+//   2: 8 x 8, 256 threads     3: 24 x 16, 768 threads
 //   4: 8 x 8, 64 threads      5: 16 x 8, 128 threads
 //   6: 16 x 16, 256 threads   7: 8 x 4, 64 threads
-// (4-7: several nodes per lane, more workgroups per CU), all advancing up to
+// (4-7: several nodes per lane, more workgroups per CU), each advancing up to
 // kSubstepBlock sub-steps per launch; single cases also take
-//   8: 32 x 8, 256 threads, one sub-step per launch
-//   9: 16 x 16, 256 threads, one sub-step per launch
-//  10: 32 x 8, 384 threads, two sub-steps per launch
-// (large grids, where the halo updates of deeper blocking cost more than
-// the loads they save)
+//   8: 32 x 8, 384 threads, one sub-step per launch
+//   9: 24 x 8, 512 threads
+//  10: 32 x 8, 448 threads, two sub-steps per launch
 constexpr int kSubstepVariants = 8;         // case-batched kernels
 constexpr int kSubstepVariantsSingle = 11;  // single-case kernels
 // sub-steps a launch of `variant` advances at most (callers step by it)
 int substep_block(int variant);
+// The variant a single case takes unless tuned: the least time by the
+// measured cost of each tile and the rounds the grid's tiles need on the
+// compute units.
 template <class R>
-constexpr int default_substep_variant() {
-  return sizeof(R) == 8 ? 1 : 3;  // fastest at the 512 x 128 grid (hlbm_tune measures)
-}
+int default_substep_variant(int nux, int nuy);
+// ... and a batch: of 16 lattices of 256^2 to 1024^2 308 us per step in FP32
+// and 491 in FP64 (32 x 8 tiles 347 and 545), of 12 of 320^2 439 in FP64 (432)
+constexpr int kBatchSubstepVariant = 3;
 // tile shape of a sub-step variant (work lists of the batched kernel)
 void substep_tile(int variant, int *tx, int *ty);
 

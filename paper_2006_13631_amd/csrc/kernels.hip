@@ -481,20 +481,13 @@ __device__ __forceinline__ int ring_slot(int gi, int gj, int rx, int ry, int nux
   return -1;
 }
 
-// DB: two copies of the region, so that a sub-step reads one and writes the
-// other and a single barrier separates sub-steps
-template <class R, class G, bool DB = false>
-constexpr size_t substeps_lds_bytes() {
-  return sizeof(R) * (size_t)(NS * G::RN * (DB ? 2 : 1) + NS * G::NRING) + sizeof(int) * (size_t)G::RN;
-}
-// the region is double-buffered when both copies fit a CU's LDS
 template <class R, class G>
-constexpr bool substeps_double_buffer() {
-  return substeps_lds_bytes<R, G, true>() <= 160u * 1024u;
+constexpr size_t substeps_lds_bytes() {
+  return sizeof(R) * (size_t)(NS * G::RN + NS * G::NRING) + sizeof(int) * (size_t)G::RN;
 }
 
 // Advances tile t of a grid by `count` sub-steps m0 .. m0+count-1 of step k.
-template <class R, class G, int H, int NT, bool DB = false>
+template <class R, class G, int H, int NT>
 __device__ __forceinline__ void grid_substeps_block(
     const R *__restrict__ f, R *__restrict__ fout, const R *__restrict__ star_f, const R *__restrict__ star_n,
     const int *__restrict__ ncode, const GridClass<R> *__restrict__ tab, int nux, int nuy, int tiles_x, int t,
@@ -504,8 +497,8 @@ __device__ __forceinline__ void grid_substeps_block(
   constexpr int SPER = (RN + NT - 1) / NT;      // staging passes
   constexpr int PER = (G::MAXA + NT - 1) / NT;  // update passes
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  R *sl = reinterpret_cast<R *>(lds_raw);   // [RN][NS] grid f, rho u u (DB: two copies)
-  constexpr int RING = NS * RN * (DB ? 2 : 1);  // offset of the ring values
+  R *sl = reinterpret_cast<R *>(lds_raw);   // [RN][NS] grid f, rho u u
+  constexpr int RING = NS * RN;             // offset of the ring values
   R *rl = sl + RING;                        // [NRING][NS] f*, rho* u* u* on the outer ring
   int *scode = reinterpret_cast<int *>(rl + NS * G::NRING);  // 4 * class + type, -1 outside the grid
   const int x0 = (t % tiles_x) * TX - H, y0 = (t / tiles_x) * TY - H;  // region origin
@@ -555,9 +548,6 @@ __device__ __forceinline__ void grid_substeps_block(
       for (int q = 0; q < 9; ++q) sl[idx * NS + q] = v[u][q];
 #pragma unroll
       for (int a = 0; a < 3; ++a) sl[idx * NS + 9 + a] = P[a];
-      if (DB && !inside[u])  // never written by a sub-step: zero in both copies
-#pragma unroll
-        for (int a = 0; a < NS; ++a) sl[NS * RN + idx * NS + a] = R(0);
     }
   }
   __syncthreads();
@@ -578,19 +568,15 @@ __device__ __forceinline__ void grid_substeps_block(
   // sum_s C_s (rho u u)_s. On the outer ring an interpolation node reads
   // structured-derived values instead (Eq.(postcollision2_u)). Absent
   // neighbours have zero weights.
-  // Slots outside the mask M are known to carry zero weights and are skipped
-  // (the same sums: a zero-weight term adds an exact zero).
-  auto update_node = [&](auto mask, int idx, int code, const GridClass<R> &cl, int cur, R o9[9]) {
-    constexpr int M = decltype(mask)::value;
+  auto update_node = [&](int idx, int code, const GridClass<R> &cl, R o9[9]) {
     const int rx = idx % RX, ry = idx / RX;
     const int typ = code & 3;
     const int gi = x0 + rx, gj = y0 + ry;
     int row[NSLOT];
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
-      if (!((M >> s) & 1)) continue;
       const int di = s % 3 - 1, dj = s / 3 - 1;
-      row[s] = cur + (idx + dj * RX + di) * NS;
+      row[s] = (idx + dj * RX + di) * NS;
       if (typ == NODE_INTERFACE) {
         const int rs = ring_slot<G>(gi + di, gj + dj, rx + di, ry + dj, nux, nuy);
         if (rs >= 0) row[s] = RING + rs * NS;
@@ -605,8 +591,7 @@ __device__ __forceinline__ void grid_substeps_block(
       R a = R(0), ax = R(0), ay = R(0);
 #pragma unroll
       for (int s = 0; s < NSLOT; ++s) {
-        if (!((M >> s) & 1)) continue;
-        const R fq = sl[row[s] + q];
+          const R fq = sl[row[s] + q];
         a = fmad(cl.C[s], fq, a);
         if (CXd[q] != 0) ax = fmad(cl.Gx[s], fq, ax);
         if (CYd[q] != 0) ay = fmad(cl.Gy[s], fq, ay);
@@ -619,7 +604,6 @@ __device__ __forceinline__ void grid_substeps_block(
     R pxx = R(0), pxy = R(0), pyy = R(0);
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
-      if (!((M >> s) & 1)) continue;
       const R c = cl.C[s];
       pxx = fmad(c, sl[row[s] + 9], pxx);
       pxy = fmad(c, sl[row[s] + 10], pxy);
@@ -632,9 +616,6 @@ __device__ __forceinline__ void grid_substeps_block(
       o9[q] = fmad(dt_tau * wgt<R>(q), eq, o9[q]);
     }
   };
-  // copy a sub-step reads (offset into the LDS values); DB: the other copy
-  // receives its results
-  auto copy_of = [&](int sub) { return DB ? (sub & 1) * NS * RN : 0; };
   // the node codes never change within a launch: each sub-step's are read
   // before the barrier that ends the previous one
   int nidx[PER], ncd[PER];
@@ -644,7 +625,6 @@ __device__ __forceinline__ void grid_substeps_block(
   for (int sub = 0; sub < H; ++sub) {
     if (sub >= count) break;
     const R uw_now = uwv[sub];
-    const int cur = copy_of(sub), nxt = copy_of(sub + 1);
     R out[PER][9];
     int sidx[PER], scd[PER];
 #pragma unroll
@@ -658,22 +638,8 @@ __device__ __forceinline__ void grid_substeps_block(
 #pragma unroll
       for (int q = 0; q < 9; ++q) out[u][q] = R(0);
       if (__ballot(code >= 0) == 0) continue;  // nothing to update in this wave
-      // a wave whose nodes all lack the same two diagonal neighbours (the
-      // interior of either half of a split-quad grid) skips those slots;
-      // with one node per lane only, to bound the code size
-      int zd = 0;
-      if constexpr (PER == 1) {
-        const int z = code >= 0 ? (code >> 2) & 3 : kZeroDiag26 | kZeroDiag08;
-        zd = __ballot(!(z & kZeroDiag26)) == 0 ? kZeroDiag26 : __ballot(!(z & kZeroDiag08)) == 0 ? kZeroDiag08 : 0;
-      }
       if (code < 0) continue;
-      const GridClass<R> &cl = tab[code >> 4];
-      if (zd == kZeroDiag26)
-        update_node(std::integral_constant<int, 0x1FF & ~(1 << 2 | 1 << 6)>{}, idx, code, cl, cur, out[u]);
-      else if (zd == kZeroDiag08)
-        update_node(std::integral_constant<int, 0x1FF & ~(1 << 0 | 1 << 8)>{}, idx, code, cl, cur, out[u]);
-      else
-        update_node(std::integral_constant<int, 0x1FF>{}, idx, code, cl, cur, out[u]);
+      update_node(idx, code, tab[code >> 4], out[u]);
       if ((code & 3) == NODE_WALL) {
         // wall nodes: impose the lamina velocity, keep rho and f^neq
         const int rx = idx % RX, ry = idx / RX;
@@ -692,28 +658,18 @@ __device__ __forceinline__ void grid_substeps_block(
 #pragma unroll
         for (int q = 0; q < 9; ++q) out[u][q] = ew[q] + (out[u][q] - e[q]);
       }
-      if (DB) {  // the other copy: written at once, read after the barrier
-        R P[3];
-        quad_moments<R>(out[u], P);
-#pragma unroll
-        for (int q = 0; q < 9; ++q) sl[nxt + idx * NS + q] = out[u][q];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) sl[nxt + idx * NS + 9 + a] = P[a];
-      }
     }
-    if (!DB) {  // one copy: every read of the sub-step ends before the writes
-      __syncthreads();
+    __syncthreads();  // every read of the sub-step ends before the writes
 #pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int idx = sidx[u], code = scd[u];
-        if (code < 0) continue;
-        R P[3];
-        quad_moments<R>(out[u], P);
+    for (int u = 0; u < PER; ++u) {
+      const int idx = sidx[u], code = scd[u];
+      if (code < 0) continue;
+      R P[3];
+      quad_moments<R>(out[u], P);
 #pragma unroll
-        for (int q = 0; q < 9; ++q) sl[idx * NS + q] = out[u][q];
+      for (int q = 0; q < 9; ++q) sl[idx * NS + q] = out[u][q];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) sl[idx * NS + 9 + a] = P[a];
-      }
+      for (int a = 0; a < 3; ++a) sl[idx * NS + 9 + a] = P[a];
     }
     if (sub + 1 < count)
 #pragma unroll
@@ -729,13 +685,12 @@ __device__ __forceinline__ void grid_substeps_block(
         const int ci = ry * RX + rx;
         const size_t p = (size_t)gj * nux + gi;
 #pragma unroll
-        for (int q = 0; q < 9; ++q) dst[q * N + p] = sl[nxt + ci * NS + q];
+        for (int q = 0; q < 9; ++q) dst[q * N + p] = sl[ci * NS + q];
       }
     }
   }
 
   // the tile is exact: write it back
-  const int last = copy_of(count);
   for (int j = threadIdx.x; j < TX * TY; j += NT) {
     const int rx = H + j % TX, ry = H + j / TX;
     const int gi = x0 + rx, gj = y0 + ry;
@@ -743,7 +698,7 @@ __device__ __forceinline__ void grid_substeps_block(
     const int ci = ry * RX + rx;
     const size_t p = (size_t)gj * nux + gi;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) fout[q * N + p] = sl[last + ci * NS + q];
+    for (int q = 0; q < 9; ++q) fout[q * N + p] = sl[ci * NS + q];
   }
 }
 
@@ -922,9 +877,15 @@ __device__ __forceinline__ void grid_fixed_block(
   }
 }
 
-// Variants of the sub-step kernel: tile shape and workgroup size (one lane
-// per region node while staging). Variant 3's LDS fits two workgroups on a
-// CU in FP64 and more in FP32 (many small grids).
+// Variants of the sub-step kernel: tile shape and workgroup size (a lane per
+// region node where the width allows, grid_fixed_block; else several nodes
+// per lane, grid_substeps_block). A small
+// tile holds few waves per SIMD, so its sub-step is short, but works mostly
+// on its halo; a large one the other way round. Launch of four sub-steps, us
+// (32 x 8 tile before): 256 x 64 grid 8 x 8 tile 10.5 (14.7) in FP64, 8.4
+// (10.4) in FP32; 384 x 96 24 x 8 13.2 (15.2), 9.8 (10.7); 512 x 128 32 x 8
+// 15.6, 10.8; 1024 x 256 32 x 16 44.1 (56.2), 28.2 (39.1); 2048 x 512 158
+// (197), 24 x 8 in FP32 90 (128).
 template <int TXv, int TYv, int NTv, int Hv = kSubstepBlock>
 struct SubstepShape {
   using G = Region<TXv, TYv, Hv>;
@@ -936,21 +897,21 @@ template <class R, class SV, bool BATCH = false>
 constexpr size_t variant_lds_bytes() {
   using G = typename SV::G;
   if constexpr (SV::FIXED) return fixed_lds_bytes<R, G, !BATCH && fixed_double_buffer<R, G>()>();
-  else return substeps_lds_bytes<R, G, !BATCH && substeps_double_buffer<R, G>()>();
+  else return substeps_lds_bytes<R, G>();
 }
 template <int V>
 struct SubstepVariant;
-template <> struct SubstepVariant<0> : SubstepShape<16, 16, 576> {};
+template <> struct SubstepVariant<0> : SubstepShape<32, 16, 960> {};
 template <> struct SubstepVariant<1> : SubstepShape<32, 8, 640> {};
-template <> struct SubstepVariant<2> : SubstepShape<64, 4, 896> {};
-template <> struct SubstepVariant<3> : SubstepShape<16, 8, 384> {};
+template <> struct SubstepVariant<2> : SubstepShape<8, 8, 256> {};
+template <> struct SubstepVariant<3> : SubstepShape<24, 16, 768> {};
 template <> struct SubstepVariant<4> : SubstepShape<8, 8, 64> {};
 template <> struct SubstepVariant<5> : SubstepShape<16, 8, 128> {};
 template <> struct SubstepVariant<6> : SubstepShape<16, 16, 256> {};
 template <> struct SubstepVariant<7> : SubstepShape<8, 4, 64> {};
-template <> struct SubstepVariant<8> : SubstepShape<32, 8, 256, 1> {};
-template <> struct SubstepVariant<9> : SubstepShape<16, 16, 256, 1> {};
-template <> struct SubstepVariant<10> : SubstepShape<32, 8, 384, 2> {};
+template <> struct SubstepVariant<8> : SubstepShape<32, 8, 384, 1> {};
+template <> struct SubstepVariant<9> : SubstepShape<24, 8, 512> {};
+template <> struct SubstepVariant<10> : SubstepShape<32, 8, 448, 2> {};
 
 template <class R, int V>
 __global__ __launch_bounds__(SubstepVariant<V>::NT) void k_grid_substeps(
@@ -966,7 +927,7 @@ __global__ __launch_bounds__(SubstepVariant<V>::NT) void k_grid_substeps(
         f, fout, star_f, ncode, tab, nux, nuy, tiles_x, t, dt, dt_tau, uw, *dk, n_sub, m0, count, tape, wtape, widx,
         nwall);
   else
-    grid_substeps_block<R, typename SV::G, SV::H, SV::NT, substeps_double_buffer<R, typename SV::G>()>(
+    grid_substeps_block<R, typename SV::G, SV::H, SV::NT>(
         f, fout, star_f, star_n, ncode, tab, nux, nuy, tiles_x, t, dt, dt_tau, uw, *dk, n_sub, m0, count, tape, wtape,
         widx, nwall);
 }
@@ -1820,13 +1781,39 @@ void LevelKernels<T, R>::restrict_level(const T *Fprev, int nxf, int nyf, size_t
 }
 
 int substep_block(int variant) {
-  switch (variant) {
-    case 8: return SubstepVariant<8>::H;
-    case 9: return SubstepVariant<9>::H;
-    case 10: return SubstepVariant<10>::H;
-    default: return kSubstepBlock;
-  }
+  return variant == 8 ? SubstepVariant<8>::H : variant == 10 ? SubstepVariant<10>::H : kSubstepBlock;
 }
+
+template <class R>
+int default_substep_variant(int nux, int nuy) {
+  // {variant, workgroups of it a compute unit holds at once, us of a launch
+  // of four sub-steps above the launch's own 5 us for each such round}
+  struct Cost {
+    int v, res;
+    double us;
+  };
+  static const Cost f64[] = {{2, 1, 5.3}, {2, 2, 8.1}, {9, 1, 8.3}, {1, 1, 10.6}, {3, 1, 14.2}, {0, 1, 18.4}};
+  static const Cost f32[] = {{2, 1, 3.4}, {2, 2, 4.3}, {2, 3, 5.7}, {2, 4, 8.5}, {9, 1, 4.6},
+                             {9, 2, 7.4}, {1, 1, 5.7}, {3, 1, 7.2}, {0, 1, 11.3}};
+  const Cost *c = sizeof(R) == 8 ? f64 : f32;
+  const int nc = sizeof(R) == 8 ? (int)(sizeof(f64) / sizeof(Cost)) : (int)(sizeof(f32) / sizeof(Cost));
+  constexpr int cus = 256;
+  int best = 1;
+  double best_us = 0.0;
+  for (int i = 0; i < nc; ++i) {
+    int tx, ty;
+    substep_tile(c[i].v, &tx, &ty);
+    const int64_t tiles = (int64_t)((nux + tx - 1) / tx) * ((nuy + ty - 1) / ty);
+    const double us = c[i].us * (double)((tiles + (int64_t)cus * c[i].res - 1) / ((int64_t)cus * c[i].res));
+    if (i == 0 || us < best_us) {
+      best = c[i].v;
+      best_us = us;
+    }
+  }
+  return best;
+}
+template int default_substep_variant<double>(int, int);
+template int default_substep_variant<float>(int, int);
 
 void substep_tile(int variant, int *tx, int *ty) {
   switch (variant) {
@@ -1835,7 +1822,8 @@ void substep_tile(int variant, int *tx, int *ty) {
     *tx = SubstepVariant<V>::G::TX;      \
     *ty = SubstepVariant<V>::G::TY;      \
     break;
-    HLBM_TILE(1) HLBM_TILE(2) HLBM_TILE(3) HLBM_TILE(4) HLBM_TILE(5) HLBM_TILE(6) HLBM_TILE(7)
+    HLBM_TILE(1) HLBM_TILE(2) HLBM_TILE(3) HLBM_TILE(4) HLBM_TILE(5) HLBM_TILE(6) HLBM_TILE(7) HLBM_TILE(8)
+    HLBM_TILE(9) HLBM_TILE(10)
 #undef HLBM_TILE
     default:
       *tx = SubstepVariant<0>::G::TX;
@@ -1961,7 +1949,7 @@ template <class T, class R>
 void Kernels<T, R>::grid_substeps(const CaseView<T, R> &v, const R *f, R *fout, int m0, int count, hipStream_t s,
                                   R *tape, R *wtape, const int *widx, int nwall, int variant, hipEvent_t start,
                                   hipEvent_t stop) {
-  switch (variant < 0 ? default_substep_variant<R>() : variant) {
+  switch (variant < 0 ? default_substep_variant<R>(v.nux, v.nuy) : variant) {
 #define HLBM_V(V) \
   case V: grid_substeps_v<V>(v, f, fout, m0, count, s, tape, wtape, widx, nwall, start, stop); break;
     HLBM_V(1) HLBM_V(2) HLBM_V(3) HLBM_V(4) HLBM_V(5) HLBM_V(6) HLBM_V(7) HLBM_V(8) HLBM_V(9) HLBM_V(10)
@@ -2051,7 +2039,7 @@ void Kernels<T, R>::batched(BatchKernel which, const CaseView<T, R> *views, cons
       hipLaunchKernelGGL((kb_interface_donors<T, R>), g, dim3(256), 0, s, views, items);
       break;
     case BatchKernel::GridSubsteps:  // threads: the sub-step variant (-1: default)
-      switch (threads < 0 ? default_substep_variant<R>() : threads) {
+      switch (threads < 0 ? kBatchSubstepVariant : threads) {
 #define HLBM_KB(V)                                                                                                \
   hipLaunchKernelGGL((kb_grid_substeps<T, R, V>), g, dim3(SubstepVariant<V>::NT),                              \
                      (variant_lds_bytes<R, SubstepVariant<V>, true>()), s, views, items, m0)
