@@ -1116,6 +1116,9 @@ class Case final : public CaseBase {
       }
     HIPCHK(hipStreamSynchronize(s_main_));
     if (!m_yref_) {
+      build_buckets(&grid_, kBucket);  // the nodes now move, by less than a bucket
+      HIPCHK(upload(&m_bstart_, grid_.bstart.data(), grid_.bstart.size() * sizeof(int)));
+      HIPCHK(upload(&m_blist_, grid_.blist.data(), std::max<size_t>(1, grid_.blist.size()) * sizeof(int)));
       HIPCHK(upload(&m_yref_, grid_.y.data(), N * sizeof(double)));
       HIPCHK(alloc(&m_prof_, N * sizeof(double)));
       HIPCHK(alloc(&m_sx_, N * sizeof(R)));

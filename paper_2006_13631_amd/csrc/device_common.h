@@ -291,20 +291,36 @@ __device__ __forceinline__ double edge_area(double ax, double ay, double bx, dou
 __device__ inline int mesh_locate(const MeshGeom &m, double px, double py, int node[3], double lam[3]) {
   const int bi = (int)floor((px - m.bx0) / kBucket), bj = (int)floor((py - m.by0) / kBucket);
   if (bi < 0 || bj < 0 || bi >= m.bnx || bj >= m.bny) return -1;
-  const int b = bj * m.bnx + bi;
-  for (int s = m.bstart[b]; s < m.bstart[b + 1]; ++s) {
-    const int t = m.blist[s];
-    const double *q = m.txy + 6 * (size_t)t;
-    const double D = edge_area(q[0], q[1], q[2], q[3], q[4], q[5]);
-    const double l0 = edge_area(q[2], q[3], q[4], q[5], px, py) / D;
-    const double l1 = edge_area(q[4], q[5], q[0], q[1], px, py) / D;
-    const double l2 = edge_area(q[0], q[1], q[2], q[3], px, py) / D;
-    if (l0 >= -1e-12 && l1 >= -1e-12 && l2 >= -1e-12) {
-      lam[0] = l0;
-      lam[1] = l1;
-      lam[2] = l2;
-      for (int a = 0; a < 3; ++a) node[a] = m.tri[3 * (size_t)t + a];
-      return t;
+  const int b = bj * m.bnx + bi, s1 = m.bstart[b + 1];
+  // the list in eights, whose triangles are read together (one after the
+  // other, each cost two round trips to L2)
+  constexpr int NB = 8;
+  for (int s = m.bstart[b]; s < s1; s += NB) {
+    int t[NB];
+    double q[NB][6];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) t[i] = m.blist[s + i < s1 ? s + i : s1 - 1];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) q[i][c] = m.txy[6 * (size_t)t[i] + c];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (s + i >= s1) break;
+      const double D = edge_area(q[i][0], q[i][1], q[i][2], q[i][3], q[i][4], q[i][5]);
+      const double a0 = edge_area(q[i][2], q[i][3], q[i][4], q[i][5], px, py);
+      const double a1 = edge_area(q[i][4], q[i][5], q[i][0], q[i][1], px, py);
+      const double a2 = edge_area(q[i][0], q[i][1], q[i][2], q[i][3], px, py);
+      // clearly outside: no division needed to tell
+      if (a0 < -2e-12 * D || a1 < -2e-12 * D || a2 < -2e-12 * D) continue;
+      const double l0 = a0 / D, l1 = a1 / D, l2 = a2 / D;
+      if (l0 >= -1e-12 && l1 >= -1e-12 && l2 >= -1e-12) {
+        lam[0] = l0;
+        lam[1] = l1;
+        lam[2] = l2;
+        for (int a = 0; a < 3; ++a) node[a] = m.tri[3 * (size_t)t[i] + a];
+        return t[i];
+      }
     }
   }
   return -1;

@@ -370,21 +370,27 @@ bool build_mesh(int nnode, const double *xy, const int *type, int ntri, const in
     }
     g->row[p + 1] = (int)g->col.size();
   }
-  // point-location buckets
+  build_buckets(g, 1e-6);
+  return true;
+}
+
+// Point-location buckets: each lists, in increasing order, the triangles
+// whose box grown by `grow` on every side meets it.
+void build_buckets(HostGrid *g, double grow) {
   g->bx0 = g->ex0;
   g->by0 = g->ey0;
   g->bnx = (int)std::floor((g->ex1 - g->ex0) / kBucket) + 1;
   g->bny = (int)std::floor((g->ey1 - g->ey0) / kBucket) + 1;
   const size_t nb = (size_t)g->bnx * g->bny;
   std::vector<std::vector<int>> lists(nb);
-  for (int t = 0; t < ntri; ++t) {
+  for (int t = 0; t < g->ntri; ++t) {
     const double *q = &g->txy[6 * t];
     const double x0 = std::min({q[0], q[2], q[4]}), x1 = std::max({q[0], q[2], q[4]});
     const double y0 = std::min({q[1], q[3], q[5]}), y1 = std::max({q[1], q[3], q[5]});
-    const int i0 = std::max(0, (int)std::floor((x0 - g->bx0) / kBucket) - 1);
-    const int i1 = std::min(g->bnx - 1, (int)std::floor((x1 - g->bx0) / kBucket) + 1);
-    const int j0 = std::max(0, (int)std::floor((y0 - g->by0) / kBucket) - 1);
-    const int j1 = std::min(g->bny - 1, (int)std::floor((y1 - g->by0) / kBucket) + 1);
+    const int i0 = std::max(0, (int)std::floor((x0 - grow - g->bx0) / kBucket));
+    const int i1 = std::min(g->bnx - 1, (int)std::floor((x1 + grow - g->bx0) / kBucket));
+    const int j0 = std::max(0, (int)std::floor((y0 - grow - g->by0) / kBucket));
+    const int j1 = std::min(g->bny - 1, (int)std::floor((y1 + grow - g->by0) / kBucket));
     for (int j = j0; j <= j1; ++j)
       for (int i = i0; i <= i1; ++i) lists[(size_t)j * g->bnx + i].push_back(t);
   }
@@ -394,7 +400,6 @@ bool build_mesh(int nnode, const double *xy, const int *type, int ntri, const in
     g->blist.insert(g->blist.end(), lists[i].begin(), lists[i].end());
     g->bstart[i + 1] = (int)g->blist.size();
   }
-  return true;
 }
 
 }  // namespace mghlbm

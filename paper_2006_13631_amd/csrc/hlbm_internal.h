@@ -93,8 +93,7 @@ struct HostGrid {
   std::vector<int> trow, tlist, tslot;
   std::vector<int> wall_o;               // third vertex of each wall edge's triangle
   double ex0 = 0, ex1 = 0, ey0 = 0, ey1 = 0;  // bounding box of the nodes
-  // point location: unit buckets over the bounding box, each listing (in
-  // increasing order) the triangles whose box, grown by one bucket, meets it
+  // point location: unit buckets over the bounding box (build_buckets)
   double bx0 = 0, by0 = 0;
   int bnx = 0, bny = 0;
   std::vector<int> bstart, blist;
@@ -130,5 +129,11 @@ bool build_grid(int nux, int nuy, double h, double b, bool body, HostGrid *g, st
 // bounding box, a bounding box not symmetric about y = 0.
 bool build_mesh(int nnode, const double *xy, const int *type, int ntri, const int *tri, double b, double T,
                 bool body, HostGrid *g, std::string *err);
+
+// Point-location buckets of an unstructured grid: each lists, in increasing
+// order, the triangles whose box grown by `grow` on every side meets it. A
+// rigid grid needs no more than the location's tolerance (1e-6 here); the
+// nodes of a bending one move by less than a bucket.
+void build_buckets(HostGrid *g, double grow);
 
 }  // namespace mghlbm
