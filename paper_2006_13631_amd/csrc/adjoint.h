@@ -24,6 +24,10 @@ struct AdjClass {
   R C[NSLOT];
   int star;
   int type;  // NodeType of q
+  // the same without the empty slots, in slot order: slot li_s[i] with (C,
+  // Gx, Gy) = li_w[i] and bit i of li_star, padded with q itself at zero weight
+  R li_w[NLIST][3];
+  int li_s[NLIST], li_star;
 };
 
 // Everything the adjoint kernels of one reverse step read, by value.
@@ -52,8 +56,7 @@ struct AdjCtx {
   const int *wall_nodes;    // ids of the wall nodes
   const int *widx;          // per grid node: its index among the wall nodes, -1 otherwise
   const unsigned char *ntype;  // per grid node: NodeType
-  const int *acls;          // per grid node: 4 transposed stencil class + the diagonal slot
-                            // pairs it lacks (bit 0: slots 2 and 6, bit 1: 0 and 8)
+  const int *acls;          // per grid node: transposed stencil class
   const AdjClass<R> *atab;
   const double *wall_nrm;   // [2][nnode]: sum over a wall node's edges of (len/2) n
   const R *wt;              // [n][3][n_wall] wall-node moments before the velocity is imposed

@@ -278,231 +278,222 @@ __device__ __forceinline__ void wall_vjp(R rho, R ux, R uy, R uw, R u[9], R &d_u
 
 // Transposed Eq.(ulbe)/Eq.(postcollision2_u) stencil, up to kAdjBlock
 // sub-steps backwards per launch (temporal blocking, as in the forward). A
-// workgroup owns an ATX x ATY tile and stages the adjoint of the tile plus a
-// kAdjBlock-node halo (zeros outside the grid) in LDS, wall nodes already
-// pulled back through the velocity imposition of the first sub-step it
-// reverses. Reversing sub-step m updates the region grown by the number of
-// sub-steps still to go in the launch: node q applies its transposed
-// stencil class to the nine region values around it and the chain of its
-// own non-equilibrium part at the taped state U_m; the new value of a wall
-// node is at once pulled back through the imposition of sub-step m - 1.
-// Lanes are dealt over each sub-step's rectangle. Parameter partials and
-// the running sums of the structured-derived adjoints (interface nodes)
-// are taken for the tile's own nodes only.
-constexpr int ATX = 16, ATY = 4, kAdjBlock = 4, ANT = 256;
+// workgroup owns an ATX x ATY tile, one lane per node of the tile and its
+// kAdjBlock-node halo for the whole launch: the lane keeps its node's adjoint,
+// transposed weights and neighbour addresses in registers; the adjoints of
+// the region are in LDS (two copies, one barrier per sub-step), wall nodes
+// already pulled back through the velocity imposition of the first sub-step
+// the launch reverses. Reversing sub-step m updates the region grown by the
+// number of sub-steps still to go in the launch: node q applies its
+// transposed stencil to the values around it and the chain of its own
+// non-equilibrium part at the taped state U_m (read a sub-step ahead); the
+// new value of a wall node is at once pulled back through the imposition of
+// sub-step m - 1. Parameter partials and the running sums of the
+// structured-derived adjoints (interface nodes) are taken for the tile's own
+// nodes only. Bound by the chain of a sub-step (LDS reads, sums, taped
+// state); with lanes dealt afresh each sub-step over 16 x 4 tiles, classes
+// read from memory and the taped state after the barrier, a launch of four
+// took 28.4 us on the 64 x 16 grid in FP64, now 15.6.
+constexpr int kAdjBlock = 4;
+template <int TXv, int TYv>
+struct AdjTile {
+  static constexpr int TX = TXv, TY = TYv, H = kAdjBlock, RX = TX + 2 * H, RY = TY + 2 * H, RN = RX * RY;
+  static constexpr int NT = (RN + 63) / 64 * 64;
+};
+using AdjSmall = AdjTile<8, 8>;
+using AdjLarge = AdjTile<16, 16>;
 
-template <class T, class R>
-__global__ __launch_bounds__(ANT) void k_adj_substeps(AdjCtx<T, R> c, const R *__restrict__ tape0,
-                                                      const R *__restrict__ ub, R *__restrict__ ub_out, int m_hi,
-                                                      int count, AdjSubScal<R> sc, int first, int last, int slot0) {
-  constexpr int H = kAdjBlock, RX = ATX + 2 * H, RY = ATY + 2 * H, RN = RX * RY;
-  constexpr int SPER = (RN + ANT - 1) / ANT;
-  constexpr int PER = ((ATX + 2 * (H - 1)) * (ATY + 2 * (H - 1)) + ANT - 1) / ANT;
-  __shared__ R sob[RN * 9];              // adjoint of the region's grid state
-  __shared__ int scls[RN];               // acls of the node, -1 outside the grid
-  __shared__ R acc[ATX * ATY * 18];      // running sums (sf, sn) of the tile's interface nodes
+template <class T, class R, class A>
+__global__ __launch_bounds__(A::NT) void k_adj_substeps(AdjCtx<T, R> c, const R *__restrict__ tape0,
+                                                        const R *__restrict__ ub, R *__restrict__ ub_out, int m_hi,
+                                                        int count, AdjSubScal<R> sc, int first, int last, int slot0) {
+  constexpr int H = A::H, RX = A::RX, RN = A::RN, COPY = RN * 9;
+  __shared__ R sob[2 * COPY];                // adjoint of the region's grid state
+  __shared__ R acc[A::TX * A::TY * 18];      // running sums (sf, sn) of the tile's interface nodes
   const GridGeom &g = c.gg;
   const size_t N = (size_t)c.nnode;
-  const int tiles_x = (g.nux + ATX - 1) / ATX;
-  const int x0 = (blockIdx.x % tiles_x) * ATX - H, y0 = (blockIdx.x / tiles_x) * ATY - H;
+  const int tiles_x = (g.nux + A::TX - 1) / A::TX;
+  const int x0 = (blockIdx.x % tiles_x) * A::TX - H, y0 = (blockIdx.x / tiles_x) * A::TY - H;
+  const int idx = threadIdx.x, rx = idx % RX, ry = idx / RX;
+  const int gi = x0 + rx, gj = y0 + ry;
+  const bool in = idx < RN && gi >= 0 && gj >= 0 && gi < g.nux && gj < g.nuy;
+  const size_t p = in ? (size_t)gj * g.nux + gi : 0;
+  // distance outside the tile: the node is needed while that many sub-steps follow
+  const int dist = max(max(H - rx, rx - (H + A::TX - 1)), max(max(H - ry, ry - (H + A::TY - 1)), 0));
+  const bool own = in && dist == 0;
+  const int jn = (ry - H) * A::TX + (rx - H);  // of an own node
   double pA = 0.0, pW = 0.0, pT = 0.0;
-  auto own = [&](int rx, int ry) { return rx >= H && rx < H + ATX && ry >= H && ry < H + ATY; };
-  // stage: the region's adjoint, walls pulled back through sub-step m_hi's imposition
+  R v[9], f[9];
 #pragma unroll
-  for (int u = 0; u < SPER; ++u) {
-    const int idx = threadIdx.x + u * ANT;
-    if (idx >= RN) continue;
-    const int rx = idx % RX, ry = idx / RX;
-    const int gi = x0 + rx, gj = y0 + ry;
-    const bool in = gi >= 0 && gj >= 0 && gi < g.nux && gj < g.nuy;
-    const int p = in ? gj * g.nux + gi : 0;
-    R v[9];
+  for (int q = 0; q < 9; ++q) v[q] = in ? ub[q * N + p] : R(0);
+  const R *Um = tape0 + (size_t)m_hi * 9 * N;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) v[q] = in ? ub[q * N + p] : R(0);
-    scls[idx] = in ? c.acls[p] : -1;
-    if (in && c.ntype[p] == NODE_WALL) {
-      const R *wt = c.wt + (size_t)m_hi * 3 * c.n_wall;
-      const int w = c.widx[p];
-      R d_uw;
-      wall_vjp<R>(wt[w], wt[c.n_wall + w], wt[2 * c.n_wall + w], sc.uw[0], v, d_uw);
-      if (own(rx, ry)) {
-        pA += (double)d_uw * sc.duwA[0];
-        pW += (double)d_uw * sc.duwW[0];
-      }
-    }
+  for (int q = 0; q < 9; ++q) f[q] = in && dist < count ? Um[q * N + p] : R(1);
+  const AdjClass<R> &cl = c.atab[in ? c.acls[p] : 0];
+  const int typ = in ? cl.type : NODE_INTERIOR, star = in ? cl.li_star : 0;
+  // dt c_q.G of the four distinct directions, and -dt/tau C, per entry
+  R k1[NLIST], k2[NLIST], k5[NLIST], k6[NLIST], kc[NLIST];
+  int row[NLIST];
 #pragma unroll
-    for (int q = 0; q < 9; ++q) sob[idx * 9 + q] = v[q];
+  for (int i = 0; i < NLIST; ++i) {
+    const int s = cl.li_s[i];
+    const R cc = cl.li_w[i][0], gx = cl.li_w[i][1], gy = cl.li_w[i][2];
+    k1[i] = c.dt * gx;
+    k2[i] = c.dt * gy;
+    k5[i] = c.dt * (gx + gy);
+    k6[i] = c.dt * (gy - gx);
+    kc[i] = -c.dt_tau * cc;
+    row[i] = (idx + (s / 3 - 1) * RX + (s % 3 - 1)) * 9;
   }
-  for (int jn = threadIdx.x; jn < ATX * ATY; jn += ANT) {
-    const int gi = x0 + H + jn % ATX, gj = y0 + H + jn / ATX;
-    const bool iface = gi < g.nux && gj < g.nuy && c.ntype[gj * g.nux + gi] == NODE_INTERFACE;
-    const size_t p = iface ? (size_t)gj * g.nux + gi : 0;
+  const int w = typ == NODE_WALL ? c.widx[p] : 0;
+  R wm[3] = {R(1), R(0), R(0)};  // a wall node's taped moments of the sub-step being pulled back
+  auto wall_moments = [&](int m) {
+    const R *wt = c.wt + (size_t)m * 3 * c.n_wall;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) wm[a] = wt[a * c.n_wall + w];
+  };
+  if (typ == NODE_WALL) {
+    wall_moments(m_hi);
+    R d_uw;
+    wall_vjp<R>(wm[0], wm[1], wm[2], sc.uw[0], v, d_uw);
+    if (own) {
+      pA += (double)d_uw * sc.duwA[0];
+      pW += (double)d_uw * sc.duwW[0];
+    }
+  }
+  R stn[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) stn[k] = R(0);
+  if (own && typ == NODE_INTERFACE)
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      acc[jn * 18 + k] = (iface && !first) ? c.sbf[k * N + p] : R(0);
-      acc[jn * 18 + 9 + k] = (iface && !first) ? c.sbn[k * N + p] : R(0);
+      stn[k] = c.star_n[k * N + p];
+      acc[jn * 18 + k] = first ? R(0) : c.sbf[k * N + p];
+      acc[jn * 18 + 9 + k] = first ? R(0) : c.sbn[k * N + p];
     }
-  }
+  if (idx < RN)
+#pragma unroll
+    for (int q = 0; q < 9; ++q) sob[idx * 9 + q] = v[q];
   __syncthreads();
 
   for (int sub = 0; sub < count; ++sub) {
-    const int m = m_hi - sub;
-    const int ex = count - 1 - sub;
-    const int W = ATX + 2 * ex, NA = W * (ATY + 2 * ex), o = H - ex;
-    const R *Um = tape0 + (size_t)m * 9 * N;
-    R out[PER][9];
-    int at[PER];
-    bool upd[PER];
+    const int m = m_hi - sub, cur = (sub & 1) * COPY, nxt = COPY - cur;
+    const bool act = in && dist <= count - 1 - sub;
+    // the next sub-step's taped state and wall moments
+    R fnext[9];
+    const bool more = in && sub + 1 < count && dist <= count - 2 - sub;
+    const R *Up = tape0 + (size_t)(m - 1) * 9 * N;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int j = threadIdx.x + u * ANT;
-      const int rx = o + j % W, ry = o + j / W;
-      const int ci = j < NA ? ry * RX + rx : 0;
-      const int acode = j < NA ? scls[ci] : -1;  // 4 class + zero slot pairs
-      at[u] = ci;
-      upd[u] = acode >= 0;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) out[u][k] = R(0);
-      // a wave whose nodes all lack the same two diagonal neighbours skips
-      // those slots (zero weights: the sums are the same)
-      const int zl = acode >= 0 ? acode & 3 : 3;
-      const int zd = __ballot(!(zl & 1)) == 0 ? 1 : (__ballot(!(zl & 2)) == 0 ? 2 : 0);
-      if (!upd[u]) continue;
-      const size_t q = (size_t)(y0 + ry) * g.nux + (x0 + rx);
-      R f[9];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) f[k] = Um[k * N + q];
-      const AdjClass<R> &cl = c.atab[acode >> 2];
-      const int tq = cl.type, star = cl.star;
+    for (int q = 0; q < 9; ++q) fnext[q] = more ? Up[q * N + p] : R(1);
+    if (sub + 1 < count && typ == NODE_WALL) wall_moments(m - 1);
+    if (act) {
       R accF[9], accN[9], sf[9], sn[9];
 #pragma unroll
       for (int k = 0; k < 9; ++k) accF[k] = accN[k] = sf[k] = sn[k] = R(0);
-      auto gather = [&](auto mask) {
-        constexpr int M = decltype(mask)::value;
+      auto dir = [&](int k, int i) {  // dt c_k.G of entry i (k = 0: none)
+        return k == 1 ? k1[i] : k == 3 ? -k1[i] : k == 2 ? k2[i] : k == 4 ? -k2[i]
+             : k == 5 ? k5[i] : k == 7 ? -k5[i] : k == 6 ? k6[i] : -k6[i];
+      };
 #pragma unroll
-      for (int s = 0; s < NSLOT; ++s) {
-        if (!((M >> s) & 1)) continue;
-        const int ri = ci + (s / 3 - 1) * RX + (s % 3 - 1);
-        const R gx = cl.Gx[s], gy = cl.Gy[s], cc = cl.C[s];
-        const bool st_s = (star >> s) & 1;
+      for (int i = 0; i < NLIST; ++i) {
+        R ov[9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          const R ov = sob[ri * 9 + k];
-          const R st = c.dt * (R(CXd[k]) * gx + R(CYd[k]) * gy) * ov;
-          const R ct = -c.dt_tau * cc * ov;
-          if (st_s) {
-            sf[k] += st;
-            sn[k] += ct;
-          } else {
-            accF[k] += st;
-            accN[k] += ct;
+        for (int k = 0; k < 9; ++k) ov[k] = sob[cur + row[i] + k];
+        if ((star >> i) & 1) {
+#pragma unroll
+          for (int k = 0; k < 9; ++k) {
+            if (k) sf[k] += dir(k, i) * ov[k];
+            sn[k] += kc[i] * ov[k];
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < 9; ++k) {
+            if (k) accF[k] += dir(k, i) * ov[k];
+            accN[k] += kc[i] * ov[k];
           }
         }
       }
-      };
-      if (zd == 1)
-        gather(std::integral_constant<int, 0x1FF & ~(1 << 2 | 1 << 6)>{});
-      else if (zd == 2)
-        gather(std::integral_constant<int, 0x1FF & ~(1 << 0 | 1 << 8)>{});
-      else
-        gather(std::integral_constant<int, 0x1FF>{});
       // the node's own value: its f, or f* at an interface node
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
-        if (tq == NODE_INTERFACE) sf[k] += sob[ci * 9 + k];
-        else accF[k] += sob[ci * 9 + k];
+        if (typ == NODE_INTERFACE) sf[k] += v[k];
+        else accF[k] += v[k];
       }
       R e[9], rho, ux, uy, fb[9];
       moments<R>(f, rho, ux, uy);
       equilibrium<R>(rho, ux, uy, e);
       node_chain<R>(rho, ux, uy, R(0), R(0), R(0), accN, fb);
-      double dn = 0.0;
+      if (own) {
+        double dn = 0.0;
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        out[u][k] = accF[k] + fb[k];
-        dn += (double)accN[k] * (double)(f[k] - e[k]);
-      }
-      if (tq == NODE_INTERFACE) {
-        double ds = 0.0;
+        for (int k = 0; k < 9; ++k) dn += (double)accN[k] * (double)(f[k] - e[k]);
+        if (typ == NODE_INTERFACE) {
+          double ds = 0.0;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) ds += (double)sn[k] * (double)c.star_n[k * N + q];
-        dn += ds;
-      }
-      if (own(rx, ry)) {
-        // d(dt_u/tau_u)/d tau = -dt_u/tau_u^2: the collision adjoints carry -dt_u/tau_u
-        pT += dn * (-1.0 / c.tau_u);
-        if (tq == NODE_INTERFACE) {
-          const int jn = (ry - H) * ATX + (rx - H);
+          for (int k = 0; k < 9; ++k) ds += (double)sn[k] * (double)stn[k];
+          dn += ds;
 #pragma unroll
           for (int k = 0; k < 9; ++k) {
             acc[jn * 18 + k] += sf[k];
             acc[jn * 18 + 9 + k] += sn[k];
           }
         }
+        // d(dt_u/tau_u)/d tau = -dt_u/tau_u^2: the collision adjoints carry -dt_u/tau_u
+        pT += dn * (-1.0 / c.tau_u);
       }
-    }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      if (!upd[u]) continue;
-      const int ci = at[u];
-      if (sub + 1 < count) {  // pull a wall node back through sub-step m - 1's imposition
-        const int rx = ci % RX, ry = ci / RX;
-        const size_t p = (size_t)(y0 + ry) * g.nux + (x0 + rx);
-        if (c.ntype[p] == NODE_WALL) {
-          const R *wt = c.wt + (size_t)(m - 1) * 3 * c.n_wall;
-          const int w = c.widx[p];
-          R d_uw;
-          wall_vjp<R>(wt[w], wt[c.n_wall + w], wt[2 * c.n_wall + w], sc.uw[sub + 1], out[u], d_uw);
-          if (own(rx, ry)) {
-            pA += (double)d_uw * sc.duwA[sub + 1];
-            pW += (double)d_uw * sc.duwW[sub + 1];
-          }
+      for (int k = 0; k < 9; ++k) v[k] = accF[k] + fb[k];
+      if (sub + 1 < count && typ == NODE_WALL) {  // pull back through sub-step m - 1's imposition
+        R d_uw;
+        wall_vjp<R>(wm[0], wm[1], wm[2], sc.uw[sub + 1], v, d_uw);
+        if (own) {
+          pA += (double)d_uw * sc.duwA[sub + 1];
+          pW += (double)d_uw * sc.duwW[sub + 1];
         }
       }
+      if (sub + 1 < count)
 #pragma unroll
-      for (int k = 0; k < 9; ++k) sob[ci * 9 + k] = out[u][k];
+        for (int k = 0; k < 9; ++k) sob[nxt + idx * 9 + k] = v[k];
     }
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 9; ++q) f[q] = fnext[q];
+    if (sub + 1 < count) __syncthreads();
   }
 
   // the tile is exact: write it back, with the running star sums
-  for (int jn = threadIdx.x; jn < ATX * ATY; jn += ANT) {
-    const int rx = H + jn % ATX, ry = H + jn / ATX;
-    const int gi = x0 + rx, gj = y0 + ry;
-    if (gi >= g.nux || gj >= g.nuy) continue;
-    const int ci = ry * RX + rx;
-    const size_t q = (size_t)gj * g.nux + gi;
+  if (own) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) ub_out[k * N + q] = sob[ci * 9 + k];
-    if (c.ntype[q] != NODE_INTERFACE) continue;
-    R sf[9], sn[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      sf[k] = acc[jn * 18 + k];
-      sn[k] = acc[jn * 18 + 9 + k];
-      c.sbf[k * N + q] = sf[k];
-      c.sbn[k * N + q] = sn[k];
-    }
-    if (last) {
-      // donor adjoint: f* = f^eq(rho, u) + k f^neq, f^neq* = k f^neq
-      R z[12], tot[9];
-      double dk = 0.0;
+    for (int k = 0; k < 9; ++k) ub_out[k * N + p] = v[k];
+    if (typ == NODE_INTERFACE) {
+      R sf[9], sn[9];
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
-        tot[k] = sf[k] + sn[k];
-        dk += (double)tot[k] * (double)c.star_n[k * N + q];
+        sf[k] = acc[jn * 18 + k];
+        sn[k] = acc[jn * 18 + 9 + k];
+        c.sbf[k * N + p] = sf[k];
+        c.sbn[k * N + p] = sn[k];
       }
-      equilibrium_vjp<R>(c.M2[q], c.M2[N + q], c.M2[2 * N + q], sf, z[0], z[1], z[2]);
+      if (last) {
+        // donor adjoint: f* = f^eq(rho, u) + k f^neq, f^neq* = k f^neq
+        R z[12], tot[9];
+        double dk = 0.0;
 #pragma unroll
-      for (int k = 0; k < 9; ++k) z[3 + k] = c.k_neq * tot[k];
+        for (int k = 0; k < 9; ++k) {
+          tot[k] = sf[k] + sn[k];
+          dk += (double)tot[k] * (double)stn[k];
+        }
+        equilibrium_vjp<R>(c.M2[p], c.M2[N + p], c.M2[2 * N + p], sf, z[0], z[1], z[2]);
 #pragma unroll
-      for (int k = 0; k < 12; ++k) c.Z2[k * N + q] = z[k];
-      // d f^neq*/d tau = (d k/d tau) f^neq = (d k/d tau)/k f^neq*
-      pT += dk * (1.0 / (2.0 * c.tau * c.tau)) / (double)c.k_neq;
+        for (int k = 0; k < 9; ++k) z[3 + k] = c.k_neq * tot[k];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) c.Z2[k * N + p] = z[k];
+        // d f^neq*/d tau = (d k/d tau) f^neq = (d k/d tau)/k f^neq*
+        pT += dk * (1.0 / (2.0 * c.tau * c.tau)) / (double)c.k_neq;
+      }
     }
   }
-  block_accum3<ANT>(pA, pW, pT, c.part + 3 * (size_t)(slot0 + blockIdx.x));
+  __syncthreads();
+  block_accum3<A::NT>(pA, pW, pT, c.part + 3 * (size_t)(slot0 + blockIdx.x));
 }
 
 // ---- donor gather: dJ/d f_pre at lattice nodes read by bilinear donors ------------
@@ -850,20 +841,34 @@ int AdjKernels<T, R>::refill_slots(const AdjCtx<T, R> &c) {
   return (int)blocks(c.nnode, NG);
 }
 
+// 8 x 8 tiles while the grid's fit the compute units twice over: a sub-step of
+// four waves is the shortest; larger grids take 16 x 16, which spend less on
+// halos (44 % of the lanes own a node, against 25)
+static int adj_tiles(int nux, int nuy, int tx, int ty) { return ((nux + tx - 1) / tx) * ((nuy + ty - 1) / ty); }
+static bool adj_small(int nux, int nuy) {
+  return adj_tiles(nux, nuy, AdjSmall::TX, AdjSmall::TY) <= 512;
+}
 template <class T, class R>
 int AdjKernels<T, R>::substep_slots(const AdjCtx<T, R> &c) {
-  return ((c.gg.nux + ATX - 1) / ATX) * ((c.gg.nuy + ATY - 1) / ATY);
+  return adj_small(c.gg.nux, c.gg.nuy) ? adj_tiles(c.gg.nux, c.gg.nuy, AdjSmall::TX, AdjSmall::TY)
+                                       : adj_tiles(c.gg.nux, c.gg.nuy, AdjLarge::TX, AdjLarge::TY);
 }
 template <class T, class R>
 void AdjKernels<T, R>::substeps(const AdjCtx<T, R> &c, const R *tape0, const R *ub, R *ub_out, int m_hi, int count,
                                 const AdjSubScal<R> &sc, int first, int last, int slot0, hipStream_t s,
                                 hipEvent_t start, hipEvent_t stop) {
-  if (start || stop)
-    hipExtLaunchKernelGGL((k_adj_substeps<T, R>), dim3(substep_slots(c)), dim3(ANT), 0, s, start, stop, 0, c, tape0,
-                          ub, ub_out, m_hi, count, sc, first, last, slot0);
-  else
-    hipLaunchKernelGGL((k_adj_substeps<T, R>), dim3(substep_slots(c)), dim3(ANT), 0, s, c, tape0, ub, ub_out, m_hi,
-                       count, sc, first, last, slot0);
+  const dim3 grid(substep_slots(c));
+  auto launch = [&](auto tile) {
+    using A = decltype(tile);
+    if (start || stop)
+      hipExtLaunchKernelGGL((k_adj_substeps<T, R, A>), grid, dim3(A::NT), 0, s, start, stop, 0, c, tape0, ub, ub_out,
+                            m_hi, count, sc, first, last, slot0);
+    else
+      hipLaunchKernelGGL((k_adj_substeps<T, R, A>), grid, dim3(A::NT), 0, s, c, tape0, ub, ub_out, m_hi, count, sc,
+                         first, last, slot0);
+  };
+  if (adj_small(c.gg.nux, c.gg.nuy)) launch(AdjSmall{});
+  else launch(AdjLarge{});
 }
 
 template <class T, class R>

@@ -1905,15 +1905,21 @@ class Case final : public CaseBase {
         }
         at[k].star = atab[k].star;
         at[k].type = atab[k].type;
+        // (a node's neighbours are those of its own stencil: at most NLIST entries)
+        int n = 0;
+        for (int sl = 0; sl < NSLOT; ++sl) {
+          if (at[k].C[sl] == R(0) && at[k].Gx[sl] == R(0) && at[k].Gy[sl] == R(0)) continue;
+          if (n == NLIST) return fail(HLBM_E_ARG, "a grid node has more than seven stencil entries");
+          at[k].li_s[n] = sl;
+          at[k].li_w[n][0] = at[k].C[sl];
+          at[k].li_w[n][1] = at[k].Gx[sl];
+          at[k].li_w[n][2] = at[k].Gy[sl];
+          if ((at[k].star >> sl) & 1) at[k].li_star |= 1 << n;
+          ++n;
+        }
+        for (; n < NLIST; ++n) at[k].li_s[n] = SELF_SLOT;
       }
       HIPCHK(upload(&atab_, at.data(), at.size() * sizeof(AdjClass<R>)));
-      // per node: 4 class + the diagonal slot pairs its class lacks (bit 0:
-      // slots 2 and 6, bit 1: slots 0 and 8), which a wave may skip
-      for (int q = 0; q < N; ++q) {
-        const AdjClass<R> &a = at[acls[q]];
-        auto zero = [&](int s) { return a.C[s] == R(0) && a.Gx[s] == R(0) && a.Gy[s] == R(0); };
-        acls[q] = 4 * acls[q] + (zero(2) && zero(6) ? 1 : 0) + (zero(0) && zero(8) ? 2 : 0);
-      }
       HIPCHK(upload(&acls_, acls.data(), acls.size() * sizeof(int)));
       n_adj_classes_ = (int)at.size();
     }
