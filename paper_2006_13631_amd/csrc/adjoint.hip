@@ -143,49 +143,28 @@ __device__ __forceinline__ void adj_star_block(const AdjCtx<T, R> &c, int bx) {
 }
 
 // ---- refill and force adjoint -------------------------------------------------
+// Sixteen lanes per grid node: each locates one of the new nodes that may
+// read this one (further rounds of 16 where there are more), then those that
+// do are added in their row-major order, lane k taking population k. Lane 0
+// does the rest. (One lane per node took 25 us on the 64 x 16 grid in FP64,
+// this and the star part together 10.7.)
+constexpr int kRefLanes = 16;
 template <class T, class R>
 __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot0, int bx) {
-  const int q = bx * NG + threadIdx.x;
+  const int q = bx * (NG / kRefLanes) + threadIdx.x / kRefLanes, sl = threadIdx.x % kRefLanes;
+  const int base = threadIdx.x - sl;
   const size_t N = (size_t)c.nnode;
   const GridGeom &g = c.gg;
   double pA = 0.0, pW = 0.0, pT = 0.0;
   if (q < c.nnode) {
     const int i = q % g.nux, j = q / g.nux;
     const int tq = c.ncode[q] & 3;
-    // (a) this node's own type-1 refill: adjoint of the interpolated moments
-    R z[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) z[k] = R(0);
-    unsigned char flag = tq == NODE_INTERFACE ? 2 : 0;
     int kind = 0;
     if (tq != NODE_WALL) kind = refill_cell(g, c.P.ybase, c.P.ybase1, i, j).kind;
-    R ub[9];
-#pragma unroll
-    for (int s = 0; s < 9; ++s) ub[s] = c.Ub_next[s * N + q];
-    if (kind == 1) {
-      R rho, ux, uy, fneq[9];
-      lattice_bilinear<T, R>(c.Lt, c.nx, c.ny, c.plane, c.bc, grid_x(g, i), grid_y(g, c.P.ybase1, j), rho, ux,
-                             uy, fneq);
-      equilibrium_vjp<R>(rho, ux, uy, ub, z[0], z[1], z[2]);
-      double sn = 0.0;
-#pragma unroll
-      for (int s = 0; s < 9; ++s) {
-        z[3 + s] = c.k_neq * ub[s];
-        sn += (double)ub[s] * (double)fneq[s];
-      }
-      pT += sn / (2.0 * c.tau * c.tau);  // d(1 - 1/(2 tau))/d tau
-      flag |= 1;
-    }
-#pragma unroll
-    for (int k = 0; k < 12; ++k) c.Z1[k * N + q] = z[k];
-    c.zf[q] = flag;
+    const int s9 = sl < 9 ? sl : 0;  // population of this lane
+    const R ubs = c.Ub_next[s9 * N + q], uns = c.Un[s9 * N + q];
     // (b) every refill that read this node of the old grid
-    R acc[9];
-#pragma unroll
-    for (int s = 0; s < 9; ++s) acc[s] = (tq == NODE_WALL || kind == 2) ? ub[s] : R(0);
-    R un[9];
-#pragma unroll
-    for (int s = 0; s < 9; ++s) un[s] = c.Un[s * N + q];
+    R acc = (tq == NODE_WALL || kind == 2) ? ubs : R(0);
     double dsum = 0.0;
     // a new node jj lands near old row jj + delta; its triangle's rows are
     // within one (two next to the lamina) of that
@@ -198,29 +177,37 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
       jlo = max((int)ceil((double)j - 2.0 - delta) - 1, 0);
       jhi = min((int)ceil((double)j + 2.0 - delta), g.nuy - 1);
     }
-    for (int jj = jlo; jj <= jhi; ++jj) {
-      for (int ii = max(i - 1, 0); ii <= min(i + 1, g.nux - 1); ++ii) {
-        const int p = jj * g.nux + ii;
-        if ((c.ncode[p] & 3) == NODE_WALL) continue;
+    const int ilo = max(i - 1, 0), nw = min(i + 1, g.nux - 1) - ilo + 1, ncand = nw * max(jhi - jlo + 1, 0);
+    for (int c0 = 0; c0 < ncand; c0 += kRefLanes) {
+      const int cand = c0 + sl, ii = ilo + cand % nw, jj = jlo + cand / nw, pc = jj * g.nux + ii;
+      double lam1 = 0.0, dl1 = 0.0;
+      bool hit = false;
+      if (cand < ncand && (c.ncode[pc] & 3) != NODE_WALL) {
         const RefillCell r = refill_cell(g, c.P.ybase, c.P.ybase1, ii, jj);
-        if (r.kind != 3) continue;
-        int node[3];
-        double lam[3], dl[3];
-        cell_triangle(r.ci, r.cj, g.nux, r.a, r.b, node, lam, dl, r.tri);
+        if (r.kind == 3) {
+          int node[3];
+          double lam[3], dl[3];
+          cell_triangle(r.ci, r.cj, g.nux, r.a, r.b, node, lam, dl, r.tri);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          if (node[a] != q) continue;
-          const R l = R(lam[a]);
-          double d = 0.0;
-#pragma unroll
-          for (int s = 0; s < 9; ++s) {
-            const R u = c.Ub_next[s * N + p];
-            acc[s] += l * u;
-            d += (double)u * (double)un[s];
+          for (int a = 0; a < 3; ++a) {
+            if (node[a] != q) continue;
+            lam1 = lam[a];
+            // graded: the cell coordinate b = (y_{k+1} - y_k + const)/(cell height)
+            dl1 = g.gy ? dl[a] / cell_height(g, r.cj) : dl[a];
+            hit = true;
           }
-          // graded: the cell coordinate b = (y_{k+1} - y_k + const)/(cell height)
-          dsum += g.gy ? dl[a] * d / cell_height(g, r.cj) : dl[a] * d;
         }
+      }
+      unsigned hits = (unsigned)(__ballot(hit) >> base) & ((1u << kRefLanes) - 1);
+      while (hits) {
+        const int src = base + __builtin_ctz(hits);
+        hits &= hits - 1;
+        const R l = R(__shfl(lam1, src, 64));
+        const double dd = __shfl(dl1, src, 64);
+        const int ps = __shfl(pc, src, 64);
+        const R u = c.Ub_next[s9 * N + ps];
+        acc += l * u;
+        if (sl < 9) dsum += dd * ((double)u * (double)uns);
       }
     }
     // uniform: the new node's old-grid coordinate t = (y_{k+1} - y_k)/h + const
@@ -230,7 +217,9 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
     // (c) force on the lamina at t_{k+1}
     if (tq == NODE_WALL) {
       const double nx = c.wall_nrm[q], ny = c.wall_nrm[N + q];
-      R rho, ux, uy;
+      R un[9], rho, ux, uy;
+#pragma unroll
+      for (int s = 0; s < 9; ++s) un[s] = __shfl(uns, base + s, 64);
       moments<R>(un, rho, ux, uy);
       R gb[9], fb[9];
 #pragma unroll
@@ -241,10 +230,37 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
       const R rb = R(-(c.wfx * nx + c.wfy * ny) / 3.0);
       node_chain<R>(rho, ux, uy, rb, R(0), R(0), gb, fb);
 #pragma unroll
-      for (int s = 0; s < 9; ++s) acc[s] += fb[s];
+      for (int s = 0; s < 9; ++s)
+        if (s == sl) acc += fb[s];
+    }
+    if (sl < 9) c.Ubn[sl * N + q] = acc;
+    // (a) this node's own type-1 refill: adjoint of the interpolated moments
+    // (lane k writes component k; every lane computes them)
+    R z[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) z[k] = R(0);
+    unsigned char flag = tq == NODE_INTERFACE ? 2 : 0;
+    if (kind == 1) {
+      R ub[9];
+#pragma unroll
+      for (int s = 0; s < 9; ++s) ub[s] = __shfl(ubs, base + s, 64);
+      R rho, ux, uy, fneq[9];
+      lattice_bilinear<T, R>(c.Lt, c.nx, c.ny, c.plane, c.bc, grid_x(g, i), grid_y(g, c.P.ybase1, j), rho, ux,
+                             uy, fneq);
+      equilibrium_vjp<R>(rho, ux, uy, ub, z[0], z[1], z[2]);
+      double sn = 0.0;
+#pragma unroll
+      for (int s = 0; s < 9; ++s) {
+        z[3 + s] = c.k_neq * ub[s];
+        sn += (double)ub[s] * (double)fneq[s];
+      }
+      if (sl == 0) pT += sn / (2.0 * c.tau * c.tau);  // d(1 - 1/(2 tau))/d tau
+      flag |= 1;
     }
 #pragma unroll
-    for (int s = 0; s < 9; ++s) c.Ubn[s * N + q] = acc[s];
+    for (int k = 0; k < 12; ++k)
+      if (k == sl) c.Z1[k * N + q] = z[k];
+    if (sl == 0) c.zf[q] = flag;
   }
   block_accum3<NG>(pA, pW, pT, c.part + 3 * (size_t)(slot0 + bx));
 }
@@ -727,9 +743,15 @@ __global__ __launch_bounds__(NT) void k_adj_from_grid(AdjCtx<T, R> c, int slot0)
 }
 
 // ---- grid-to-lattice adjoint, grid side -------------------------------------------
+// Half a wave per grid node. Each lane locates one candidate lattice node in
+// the grid (those around the node: up to 5 x 5 on a unit grid; further
+// rounds of 32 where the spacing is wider); the candidates whose triangle
+// holds the grid node are then added in their row-major order, lane k taking
+// component k of the twelve. (One lane per grid node locating its
+// candidates in turn took 39 us on the 64 x 16 grid in FP64, this 8.1.)
 template <class T, class R>
 __global__ __launch_bounds__(NG) void k_adj_from_grid_gather(AdjCtx<T, R> c, R *__restrict__ ub, int slot0) {
-  const int q = blockIdx.x * NG + threadIdx.x;
+  const int q = blockIdx.x * (NG / 32) + (threadIdx.x >> 5), hl = threadIdx.x & 31, half = threadIdx.x & 32;
   const GridGeom &g = c.gg;
   const size_t N = (size_t)c.nnode;
   double pA = 0.0, pW = 0.0;
@@ -755,56 +777,74 @@ __global__ __launch_bounds__(NG) void k_adj_from_grid_gather(AdjCtx<T, R> c, R *
     const int xhi = min((int)ceil(xb) + 1, c.k2_x0 + c.k2_w - 1);
     const int ylo = max((int)floor(ya) - 1, ybot);
     const int yhi = min((int)ceil(yb) + 1, ytop);
-    R zs[12], zd[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) zs[k] = zd[k] = R(0);
-    bool any = false;
-    const size_t zp = (size_t)c.k2_w * c.k2_h;
     // no candidate can be set from the grid when all of them lie strictly
     // inside the rectangle (not on its edge) or outside both rectangles
     const StepParams &P = c.P;
     const bool deep = xlo > P.ix0 && xhi < P.ix1 && ylo > P.iy0 && yhi < P.iy1;
     const bool away = xhi < min(P.ix0, P.pix0) || xlo > max(P.ix1, P.pix1) || yhi < min(P.iy0, P.piy0) ||
                       ylo > max(P.iy1, P.piy1);
-    for (int yl = (deep || away) ? yhi + 1 : ylo; yl <= yhi; ++yl) {
-      for (int xl = xlo; xl <= xhi; ++xl) {
-        if (!from_grid_target(c.P, xl, yl)) continue;
+    const int nw = xhi - xlo + 1, ncand = (deep || away || nw < 1) ? 0 : nw * max(yhi - ylo + 1, 0);
+    R zs = R(0), zd = R(0);  // component hl of the twelve
+    bool any = false;
+    const size_t zp = (size_t)c.k2_w * c.k2_h;
+    for (int c0 = 0; c0 < ncand; c0 += 32) {
+      const int cand = c0 + hl;
+      const int xl = xlo + cand % nw, yl = ylo + cand / nw;
+      R l = R(0), d = R(0);
+      int at = 0;
+      bool hit = false;
+      if (cand < ncand && from_grid_target(c.P, xl, yl)) {
         int ci, cj, tri, node[3];
         double a, b, lam[3], dl[3];
         lattice_node_cell(g, c.P.ybase, xl, yl, ci, cj, a, b, tri);
         cell_triangle(ci, cj, g.nux, a, b, node, lam, dl, tri);
-        const size_t at = (size_t)(yl - ybot) * c.k2_w + (xl - c.k2_x0);
+        at = (yl - ybot) * c.k2_w + (xl - c.k2_x0);
 #pragma unroll
         for (int n = 0; n < 3; ++n) {
           if (node[n] != q) continue;
           // graded: d b/d y_k = -1/(cell height) per cell (uniform: -1/h, below)
-          const R l = R(lam[n]), d = R(g.gy ? dl[n] / cell_height(g, cj) : dl[n]);
-#pragma unroll
-          for (int k = 0; k < 12; ++k) {
-            const R z = c.Z3[k * zp + at];
-            zs[k] += l * z;
-            zd[k] += d * z;
-          }
-          any = true;
+          l = R(lam[n]);
+          d = R(g.gy ? dl[n] / cell_height(g, cj) : dl[n]);
+          hit = true;
+        }
+      }
+      unsigned hits = (unsigned)(__ballot(hit) >> half);
+      any = any || hits;
+      while (hits) {
+        const int src = half + __builtin_ctz(hits);
+        hits &= hits - 1;
+        const R ls = __shfl(l, src, 64), ds = __shfl(d, src, 64);
+        const int as = __shfl(at, src, 64);
+        if (hl < 12) {
+          const R z = c.Z3[hl * zp + as];
+          zs += ls * z;
+          zd += ds * z;
         }
       }
     }
     if (any) {
-      R f[9], e[9], rho, ux, uy, fneq[9], fb[9];
+      R f[9], e[9], rho, ux, uy, fneq[9], fb[9], z[12], zdv[12];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        z[k] = __shfl(zs, half + k, 64);
+        zdv[k] = __shfl(zd, half + k, 64);
+      }
 #pragma unroll
       for (int k = 0; k < 9; ++k) f[k] = c.U0[k * N + q];
       moments<R>(f, rho, ux, uy);
       equilibrium<R>(rho, ux, uy, e);
 #pragma unroll
       for (int k = 0; k < 9; ++k) fneq[k] = f[k] - e[k];
-      node_chain<R>(rho, ux, uy, zs[0], zs[1], zs[2], zs + 3, fb);
+      node_chain<R>(rho, ux, uy, z[0], z[1], z[2], z + 3, fb);
+      if (hl == 0) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) ub[k * N + q] += fb[k];
-      // uniform: the lattice node's grid coordinate t = (y - y_k)/h + const
-      const double dsum = dot12<R>(zd, rho, ux, uy, fneq);
-      const double hs = g.gy ? 1.0 : g.h;
-      pA += dsum * (-c.dyA / hs);
-      pW += dsum * (-c.dyW / hs);
+        for (int k = 0; k < 9; ++k) ub[k * N + q] += fb[k];
+        // uniform: the lattice node's grid coordinate t = (y - y_k)/h + const
+        const double dsum = dot12<R>(zdv, rho, ux, uy, fneq);
+        const double hs = g.gy ? 1.0 : g.h;
+        pA += dsum * (-c.dyA / hs);
+        pW += dsum * (-c.dyW / hs);
+      }
     }
   }
   block_accum3<NG>(pA, pW, 0.0, c.part + 3 * (size_t)(slot0 + blockIdx.x));
@@ -838,7 +878,7 @@ void AdjKernels<T, R>::star_refill(const AdjCtx<T, R> &c, int slot0, hipStream_t
 
 template <class T, class R>
 int AdjKernels<T, R>::refill_slots(const AdjCtx<T, R> &c) {
-  return (int)blocks(c.nnode, NG);
+  return (int)blocks(c.nnode, NG / kRefLanes);
 }
 
 // 8 x 8 tiles while the grid's fit the compute units twice over: a sub-step of
@@ -907,7 +947,7 @@ void AdjKernels<T, R>::from_grid(const AdjCtx<T, R> &c, int slot0, hipStream_t s
 
 template <class T, class R>
 int AdjKernels<T, R>::from_grid_gather_slots(const AdjCtx<T, R> &c) {
-  return (int)blocks(c.nnode, NG);
+  return (int)blocks(c.nnode, NG / 32);
 }
 template <class T, class R>
 void AdjKernels<T, R>::from_grid_gather(const AdjCtx<T, R> &c, R *ub, int slot0, hipStream_t s) {
