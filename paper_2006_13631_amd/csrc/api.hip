@@ -79,6 +79,28 @@ hipError_t stage_planes(double *out, size_t per, double *buf, size_t cap, hipStr
   return hipStreamSynchronize(s);
 }
 
+// Device buffer a handle keeps for reading its state: at most this many
+// doubles, so a read allocates nothing after the first (an allocation and
+// its release cost 100 us and wait for the whole device) and a large state
+// goes through it in pieces.
+constexpr size_t kStageElems = ((size_t)16 << 20) / sizeof(double);
+
+// Lattice buffer src (planes `plane` apart) as packed FP64 [9][nodes] in
+// host memory, through the device buffer `stage` of `cap` doubles.
+template <class T, class R>
+hipError_t read_lattice(const T *src, size_t plane, size_t nodes, double *out, double *stage, size_t cap,
+                        hipStream_t s) {
+  if (9 * nodes <= cap) {
+    Kernels<T, R>::lattice_to_f64(src, stage, plane, nodes, s);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(out, stage, 9 * nodes * sizeof(double), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  }
+  return stage_planes(out, nodes, stage, cap, s, [&](int q, size_t a, size_t n, double *dst) {
+    Kernels<T, R>::lattice_stage_f64(src + (size_t)q * plane + a, dst, n, q, s);
+  });
+}
+
 std::string g_create_error;
 
 constexpr double kMargin = 2.0;  // inset of the fictitious rectangle (lattice units)
@@ -380,7 +402,6 @@ class Case final : public CaseBase {
     if (two_step_) {
       HIPCHK(alloc(&lat_[2], 9 * plane_ * sizeof(T)));
       Kernels<T, R>::fill_rest((T *)lat_[2], plane_, nullptr, 0, s_main_);
-      HIPCHK(build_tile_lists());
     }
     for (int i = 0; i < 3; ++i) phys_[i] = lat_[i];
     Kernels<T, R>::fill_rest((T *)lat_[0], plane_, has_grid_ ? (R *)gbuf_[0] : nullptr, N, s_main_);
@@ -550,10 +571,8 @@ class Case final : public CaseBase {
     // path that follows them (both read only the lattice of t_k or t_{k+1})
     const bool fuse = has_grid_ && !two;
     if (timing_ == 2)
-      Kernels<T, R>::stream_collide2(v, s_main_, tev_[tslot_][8], tev_[tslot_][2], tile_list(two_step_order_),
-                                     n_tiles_, fuse);
-    else
-      Kernels<T, R>::stream_collide2(v, s_main_, nullptr, nullptr, tile_list(two_step_order_), n_tiles_, fuse);
+      Kernels<T, R>::stream_collide2(v, s_main_, tev_[tslot_][8], tev_[tslot_][2], two_step_order_, fuse);
+    else Kernels<T, R>::stream_collide2(v, s_main_, nullptr, nullptr, two_step_order_, fuse);
     if (has_grid_) {
       ENQ(enqueue_grid_path(v, fuse, v.B));
       if (two) ENQ(join());
@@ -676,11 +695,11 @@ class Case final : public CaseBase {
   }
 
   int sync() override {
+    // the flag follows the steps into pinned memory: one wait for both
+    HIPCHK(hipMemcpyAsync(hflag_, flag_, sizeof(int), hipMemcpyDeviceToHost, s_main_));
     HIPCHK(hipStreamSynchronize(s_main_));
     pending_ = false;
-    int flag = 0;
-    HIPCHK(hipMemcpy(&flag, flag_, sizeof(int), hipMemcpyDeviceToHost));
-    return flag_status(flag);
+    return flag_status(*hflag_);
   }
 
   void drain() override {
@@ -739,13 +758,9 @@ class Case final : public CaseBase {
     HIPCHK(hipStreamSynchronize(s_main_));
     if (which == HLBM_STATE_LATTICE) {
       if (bytes != 9 * nodes_ * sizeof(double)) return fail(HLBM_E_ARG, "lattice state size mismatch");
-      double *tmp = nullptr;
-      HIPCHK(hipMalloc(&tmp, bytes));
-      Kernels<T, R>::lattice_to_f64((const T *)lat_[0], tmp, plane_, nodes_, s_main_);
-      hipError_t e = hipMemcpyAsync(buf, tmp, bytes, hipMemcpyDeviceToHost, s_main_);
-      if (e == hipSuccess) e = hipStreamSynchronize(s_main_);
-      (void)hipFree(tmp);
-      HIPCHK(e);
+      const size_t cap = std::min(kStageElems, 9 * nodes_);
+      if (!stage_) HIPCHK(alloc(&stage_, cap * sizeof(double)));
+      HIPCHK((read_lattice<T, R>((const T *)lat_[0], plane_, nodes_, (double *)buf, stage_, cap, s_main_)));
       return HLBM_OK;
     }
     if (which == HLBM_STATE_GRID) {
@@ -837,8 +852,8 @@ class Case final : public CaseBase {
   int force(double *hist, int64_t cap, int64_t *n_out, double t0, double t1, double th[2]) override {
     HIPCHK(hipStreamSynchronize(s_main_));
     const int64_t n = has_grid_ ? k_ : 0;
-    std::vector<double> hbuf(2 * std::max<int64_t>(n, 1));
-    if (n > 0) HIPCHK(hipMemcpy(hbuf.data(), hist_, 2 * n * sizeof(double), hipMemcpyDeviceToHost));
+    std::vector<double> hbuf(hist || th ? 2 * std::max<int64_t>(n, 1) : 0);  // a call for the length alone reads nothing
+    if (n > 0 && !hbuf.empty()) HIPCHK(hipMemcpy(hbuf.data(), hist_, 2 * n * sizeof(double), hipMemcpyDeviceToHost));
     if (th) {
       if (!(d_.omega > 0.0)) return fail(HLBM_E_ARG, "no oscillation to fit");
       const double period = 2.0 * M_PI / d_.omega;
@@ -1247,8 +1262,7 @@ class Case final : public CaseBase {
     if (two_step_) {  // the two-step kernel's tile order (writes B and C, both free between pairs)
       float best2 = 3e38f;
       for (int ord : {0, 1}) {
-        const float ms = timed(
-            s_main_, [&] { Kernels<T, R>::stream_collide2(v, s_main_, nullptr, nullptr, tile_list(ord), n_tiles_); });
+        const float ms = timed(s_main_, [&] { Kernels<T, R>::stream_collide2(v, s_main_, nullptr, nullptr, ord); });
         if (e == hipSuccess && ms < best2) {
           best2 = ms;
           two_step_order_ = ord;
@@ -1538,26 +1552,6 @@ class Case final : public CaseBase {
         if (dist(j + 1, up) > kMargin - 1e-6 && dist(j, up) < dmax) next_fits_ = false;
     }
   }
-
-  // Launch positions of the two-step tiles in contiguous runs per XCD, each
-  // run starting three tile rows and five tiles further along (measured on
-  // 2048^2 against other offsets); a count not divisible by 8 stays in turn.
-  static std::vector<int> deal_tiles(const std::vector<int> &tiles, int tiles_x) {
-    const int n = (int)tiles.size(), per = n / 8;
-    if (n % 8) return tiles;
-    std::vector<int> o(n);
-    for (int j = 0; j < n; ++j) o[j] = tiles[(j % 8) * per + (j / 8 + (j % 8) * (3 * tiles_x + 5)) % per];
-    return o;
-  }
-  hipError_t build_tile_lists() {
-    const int tx = (cfg_.nx + kTwoStepTX - 1) / kTwoStepTX, ty = (cfg_.ny + kTwoStepTY - 1) / kTwoStepTY;
-    std::vector<int> all(tx * ty);
-    for (int t = 0; t < tx * ty; ++t) all[t] = t;
-    n_tiles_ = tx * ty;
-    const std::vector<int> o = deal_tiles(all, tx);
-    return upload(&tiles_dealt_, o.data(), o.size() * sizeof(int));
-  }
-  const int *tile_list(int order) const { return order == 1 ? tiles_dealt_ : nullptr; }
 
   StepParams params_at(int64_t k) const {
     StepParams P;
@@ -2098,12 +2092,11 @@ class Case final : public CaseBase {
   int sub_n_[kTimingRing] = {};
   int tslot_ = 0;
   int timing_ = 0;  // 1: every kernel, 2: the stream-collide only
+  double *stage_ = nullptr;  // device staging of state reads (read_lattice)
   int outside_rows_ = 0;    // grid rows at either end a step may move out of the old grid
   bool next_fits_ = false;  // the refill may write the next step's interpolation nodes
   int next_targets_ = 0;    // most lattice interpolation nodes of any step
   bool next_done_ = false;  // the next step's are written already (never between calls)
-  int *tiles_dealt_ = nullptr;  // two-step tiles, dealt to the XCDs in runs
-  int n_tiles_ = 0;
   int substep_variant_ = -1;  // grid sub-step kernel variant (-1: the default for R)
   int lattice_threads_ = kLatticeThreads, lattice_rows_ = kLatticeRows;  // stream-collide launch shape
   int lattice_order_ = 0;  // 1: stream-collide rows banded by XCD
@@ -2150,7 +2143,7 @@ class Case final : public CaseBase {
   double *hist_ = nullptr;
   int64_t *dk_ = nullptr;
   int *flag_ = nullptr;
-  int *hflag_ = nullptr;          // pinned: the flag as last copied by step_async
+  int *hflag_ = nullptr;          // pinned: the flag as last copied by step_async or sync
   hipEvent_t ev_flag_ = nullptr;  // recorded after that copy
   bool flag_copied_ = false;      // a copy has been enqueued
   bool pending_ = false;          // steps enqueued by step_async not yet waited for
@@ -2865,13 +2858,8 @@ class MultiLevel final : public CaseBase {
     const size_t nodes = (size_t)c.nx * c.ny;
     if (bytes != 9 * nodes * sizeof(double)) return fail(HLBM_E_ARG, "level state size mismatch");
     HIPCHK(hipStreamSynchronize(s_));
-    double *tmp = nullptr;
-    HIPCHK(hipMalloc(&tmp, bytes));
-    Kernels<T, R>::lattice_to_f64((const T *)c.lat[0], tmp, c.plane, nodes, s_);
-    hipError_t e = hipMemcpyAsync(buf, tmp, bytes, hipMemcpyDeviceToHost, s_);
-    if (e == hipSuccess) e = hipStreamSynchronize(s_);
-    (void)hipFree(tmp);
-    HIPCHK(e);
+    if (!stage_) HIPCHK(alloc(&stage_, kStageElems * sizeof(double)));
+    HIPCHK((read_lattice<T, R>((const T *)c.lat[0], c.plane, nodes, (double *)buf, stage_, kStageElems, s_)));
     return HLBM_OK;
   }
 
@@ -3101,6 +3089,7 @@ class MultiLevel final : public CaseBase {
   hlbm_config fine_cfg_{};
   std::unique_ptr<Case<T, R>> fine_;
   Level lev_[kMaxLevels];
+  double *stage_ = nullptr;  // device staging of state reads (read_lattice)
   hipStream_t s_ = nullptr;
   hipGraphExec_t gexec_[2] = {nullptr, nullptr};
   bool use_graphs_ = true;

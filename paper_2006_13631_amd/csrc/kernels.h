@@ -176,12 +176,12 @@ struct Kernels {
                              bool donors = false);
   // two steps t_k -> t_{k+2} in one launch (tile of kTwoStepTX x kTwoStepTY
   // nodes, the first step on the tile and a one-node ring kept in LDS);
-  // needs nx >= kTwoStepTX + 2 and ny >= kTwoStepTY + 2; order: the n tiles
-  // of the launch (device memory, launch position to tile or -1; null: all
-  // tiles in turn, row by row); donors: as for stream_collide
+  // needs nx >= kTwoStepTX + 2 and ny >= kTwoStepTY + 2; order 1: the
+  // tiles are dealt to the XCDs in contiguous runs of rows, each XCD
+  // starting at a different offset (0: in turn, row by row); donors: as
+  // for stream_collide
   static void stream_collide2(const CaseView<T, R> &v, hipStream_t s, hipEvent_t start = nullptr,
-                              hipEvent_t stop = nullptr, const int *order = nullptr, int n = 0,
-                              bool donors = false);
+                              hipEvent_t stop = nullptr, int order = 0, bool donors = false);
   static void lattice_from_grid(const CaseView<T, R> &v, const R *grid, hipStream_t s);
   static void interface_donors(const CaseView<T, R> &v, hipStream_t s);
   // one sub-step m of an unstructured grid (Eq.(ulbe), Eq.(postcollision2_u)),
