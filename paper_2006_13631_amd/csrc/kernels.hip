@@ -362,6 +362,21 @@ __global__ __launch_bounds__(256) void kb_lattice_from_grid(const CaseView<T, R>
   lattice_from_grid_block<T, R>(v, v.lat[k & 1], v.grid[grid_cur(v, k)], k, it.y, it.z);
 }
 
+// A value of another of the four lanes of a quad, by a register move (a
+// shuffle would go through LDS): CTRL holds two bits per lane, the lane it
+// reads.
+template <int CTRL>
+__device__ __forceinline__ float quad_lane(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double quad_lane(double x) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, true));
+}
+constexpr int kQuad0 = 0x00, kQuad1 = 0x55, kQuad2 = 0xAA, kQuad3 = 0xFF;  // lane 0 .. 3 to all four
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;
+
 // ---- K4 prologue: structured-derived values at the grid's outer nodes ----------
 // f* = f^eq,s + (1 - 1/(2 tau_s)) f^neq,s and f^neq* from the lattice at t_{k+1}
 // (pre-collision), held over the n sub-steps (Eq.(postcollision2_u)). Four
@@ -393,8 +408,8 @@ __device__ __forceinline__ void interface_donors_block(const CaseView<T, R> &v, 
   }
 #pragma unroll
   for (int r = 0; r < 12; ++r) {
-    acc[r] += __shfl_xor(acc[r], 1, 64);
-    acc[r] += __shfl_xor(acc[r], 2, 64);
+    acc[r] += quad_lane<kQuadXor1>(acc[r]);
+    acc[r] += quad_lane<kQuadXor2>(acc[r]);
   }
   if (!valid) return;
   R e[9];
@@ -592,7 +607,7 @@ __device__ __forceinline__ void grid_substeps_block(
       R a = R(0), ax = R(0), ay = R(0);
 #pragma unroll
       for (int s = 0; s < NSLOT; ++s) {
-          const R fq = sl[row[s] + q];
+        const R fq = sl[row[s] + q];
         a = fmad(cl.C[s], fq, a);
         if (CXd[q] != 0) ax = fmad(cl.Gx[s], fq, ax);
         if (CYd[q] != 0) ay = fmad(cl.Gy[s], fq, ay);
@@ -1267,12 +1282,9 @@ __device__ __forceinline__ void outside_block(const CaseView<T, R> &v, const T *
     donor_corner<T, R>(A, v.nx, v.ny, v.plane, v.bc, X, Ynew, d, acc);
   }
 #pragma unroll
-  for (int c = 0; c < 12; ++c) {
-    const int l = threadIdx.x & 60;
-    const R a0 = __shfl(acc[c], l, 64), a1 = __shfl(acc[c], l + 1, 64), a2 = __shfl(acc[c], l + 2, 64),
-            a3 = __shfl(acc[c], l + 3, 64);
-    acc[c] = ((a0 + a1) + a2) + a3;
-  }
+  for (int c = 0; c < 12; ++c)
+    acc[c] = ((quad_lane<kQuad0>(acc[c]) + quad_lane<kQuad1>(acc[c])) + quad_lane<kQuad2>(acc[c])) +
+             quad_lane<kQuad3>(acc[c]);
   if (!valid) return;
   R e[9], rho = R(0);
   equilibrium<R>(acc[0], acc[1], acc[2], e);
@@ -1340,46 +1352,41 @@ __device__ __forceinline__ void next_from_grid_block(const CaseView<T, R> &v, T 
     y = r < lo ? Q.piy0 + r : max(Q.piy0, Q.iy1 + 1) + (r - lo);
   }
   const bool valid = from_grid_target(Q, x, y);
-  R f[9], e[9], r = R(0), vx = R(0), vy = R(0);
-  double lam[3] = {0.0, 0.0, 0.0};
+  R e[9], acc[12];  // this lane's corner, weighted: rho, u_x, u_y, f^neq
 #pragma unroll
-  for (int q = 0; q < 9; ++q) f[q] = e[q] = R(0);
-  if (valid) {
+  for (int c = 0; c < 12; ++c) acc[c] = R(0);
+  if (valid && a < 3) {
     const GridGeom gg{v.nux, v.nuy, v.h, v.xc, v.half_b, v.half_T, v.body, v.gx, v.gy};
     int node[3], ci, cj, tri;
-    double ca, cb, dlam[3];
+    double ca, cb, lam[3], dlam[3];
     lattice_node_cell(gg, Q.ybase, x, y, ci, cj, ca, cb, tri);
     cell_triangle(ci, cj, v.nux, ca, cb, node, lam, dlam, tri);
-    if (a < 3) {
-      const int p = a == 0 ? node[0] : a == 1 ? node[1] : node[2];
-      if ((v.ncode[p] & 3) == NODE_WALL) {
+    const int p = a == 0 ? node[0] : a == 1 ? node[1] : node[2];
+    const R l = R(a == 0 ? lam[0] : a == 1 ? lam[1] : lam[2]);
+    R f[9], r, vx, vy;
+    if ((v.ncode[p] & 3) == NODE_WALL) {
 #pragma unroll
-        for (int q = 0; q < 9; ++q) f[q] = fo[(size_t)q * v.nnode + p];
-      } else {
-        refill_inside<T, R>(v, fo, P, p, f);
-      }
-      moments<R>(f, r, vx, vy);
-      equilibrium<R>(r, vx, vy, e);
+      for (int q = 0; q < 9; ++q) f[q] = fo[(size_t)q * v.nnode + p];
+    } else {
+      refill_inside<T, R>(v, fo, P, p, f);
     }
+    moments<R>(f, r, vx, vy);
+    equilibrium<R>(r, vx, vy, e);
+    acc[0] = l * r;
+    acc[1] = l * vx;
+    acc[2] = l * vy;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) acc[3 + q] = l * (f[q] - e[q]);
   }
-  R rho = R(0), ux = R(0), uy = R(0), fneq[9];
 #pragma unroll
-  for (int q = 0; q < 9; ++q) fneq[q] = R(0);
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {  // corner c from lane c of the four
-    const int src = (threadIdx.x & 60) + c;
-    const R l = R(lam[c]);
-    rho += l * __shfl(r, src, 64);
-    ux += l * __shfl(vx, src, 64);
-    uy += l * __shfl(vy, src, 64);
-#pragma unroll
-    for (int q = 0; q < 9; ++q) fneq[q] += l * (__shfl(f[q], src, 64) - __shfl(e[q], src, 64));
-  }
-  if (!valid || a != 0) return;
-  equilibrium<R>(rho, ux, uy, e);
+  for (int c = 0; c < 12; ++c)
+    acc[c] = (quad_lane<kQuad0>(acc[c]) + quad_lane<kQuad1>(acc[c])) + quad_lane<kQuad2>(acc[c]);
+  if (!valid) return;
+  equilibrium<R>(acc[0], acc[1], acc[2], e);
   const size_t c = (size_t)y * v.nx + x;
 #pragma unroll
-  for (int q = 0; q < 9; ++q) Stor<T>::st(next, q * v.plane + c, q, e[q] + v.g_post * fneq[q]);
+  for (int q = 0; q < 9; ++q)
+    if ((q & 3) == a) Stor<T>::st(next, q * v.plane + c, q, e[q] + v.g_post * acc[3 + q]);
 }
 
 template <class T, class R>
@@ -1534,8 +1541,8 @@ __global__ __launch_bounds__(256) void k_force(const R *__restrict__ f, const Wa
 // `next`, a launch of its own otherwise; the others refill the grid. The
 // long dependency chains come first. The launch is bound by those chains
 // (counter, parameters, node, its three corners): 9.7 us on the 512 x 128
-// grid in FP64 and 5.8 for the interpolation nodes' own launch, 13.0
-// together; on 64 x 32 nodes 6.7 and 5.0, 8.5 together; on 1024 x 256 20.3
+// grid in FP64 and 5.8 for the interpolation nodes' own launch, 12.1
+// together; on 64 x 32 nodes 6.7 and 5.0, 7.8 together; on 1024 x 256 20.3
 // and 8.5, 20.5 together. The grid's form (0 uniform, 1 graded, 2 any
 // triangulation) is a template argument: a kernel holding all three took
 // 14.5 us. Every workgroup reads the step
