@@ -336,7 +336,6 @@ class Case final : public CaseBase {
           t.Gy[s] = (R)g.Gy[s];
         }
         auto zero = [&](int s) { return t.C[s] == R(0) && t.Gx[s] == R(0) && t.Gy[s] == R(0); };
-        t.zero_diag = (zero(2) && zero(6) ? kZeroDiag26 : 0) | (zero(0) && zero(8) ? kZeroDiag08 : 0);
         int n = 0;
         for (int s = 0; s < NSLOT; ++s) {
           if (zero(s)) continue;
@@ -354,11 +353,11 @@ class Case final : public CaseBase {
       }
       if (!grid_.mesh) {
         HIPCHK(upload(&tab_, tab.data(), tab.size() * sizeof(GridClass<R>)));
-        // node codes: 16 class + 4 zero_diag + type (static: the grid moves rigidly)
+        // node codes: 4 * class + type (static: the grid moves rigidly)
         std::vector<int> code(grid_.cls.size());
         for (size_t p = 0; p < code.size(); ++p) {
           const int k = grid_.cls[p];
-          code[p] = k >= 0 ? 16 * k + 4 * tab[k].zero_diag + tab[k].type : -1;
+          code[p] = k >= 0 ? 4 * k + tab[k].type : -1;
         }
         HIPCHK(upload(&ncode_, code.data(), code.size() * sizeof(int)));
       }

@@ -50,17 +50,11 @@ struct GridClass {
   R Gy[NSLOT];      // y weights of the streaming matrix
   R C[NSLOT];       // collision matrix C_ik
   int type;         // NodeType
-  int zero_diag;    // bit 0: slots 2 and 6 (the (+1,-1) and (-1,+1)
-                    // neighbours) carry zero weights; bit 1: slots 0 and 8
   // the same weights without the empty slots, in slot order: slot li_s[i]
   // with (C, Gx, Gy) = li_w[i], padded with the node itself at zero weight
   R li_w[NLIST][3];
   int li_s[NLIST];
 };
-
-// slots a split-quad node lacks: the two diagonal neighbours across the
-// diagonals its cells are not split along
-constexpr int kZeroDiag26 = 1, kZeroDiag08 = 2;
 
 struct WallEdge {
   int a, b;         // node indices

@@ -457,11 +457,12 @@ __global__ __launch_bounds__(256) void kb_interface_donors(const CaseView<T, R> 
 // keeps the structured-derived values of nodes on the grid's outer ring and
 // the stencil class and type of each node. Sub-step s updates the region
 // grown by count-1-s around the tile, so after `count` sub-steps the tile is
-// exact and only it is written back. In every sub-step the lanes are dealt
-// afresh over that shrinking rectangle, so no wave works on nodes outside
-// it; stencil coefficients are read from the class table (interior nodes
-// share one class, so the reads are cache broadcasts). Tiles are dealt to
-// the eight XCDs in contiguous bands.
+// exact and only it is written back. Workgroups with a lane per region node
+// keep the lanes on their nodes (grid_fixed_block); the others deal them
+// afresh over that shrinking rectangle in every sub-step, so no wave works
+// on nodes outside it, and read stencil coefficients from the class table
+// (interior nodes share one class, so the reads are cache broadcasts). Tiles
+// are dealt to the eight XCDs in contiguous bands.
 constexpr int NS = 13;  // LDS doubles (or floats) per node: f[9], rho u_x u_x, rho u_x u_y, rho u_y u_y, pad
 
 // the products rho u_x u_x, rho u_x u_y, rho u_y u_y of f's moments (the
@@ -655,7 +656,7 @@ __device__ __forceinline__ void grid_substeps_block(
       for (int q = 0; q < 9; ++q) out[u][q] = R(0);
       if (__ballot(code >= 0) == 0) continue;  // nothing to update in this wave
       if (code < 0) continue;
-      update_node(idx, code, tab[code >> 4], out[u]);
+      update_node(idx, code, tab[code >> 2], out[u]);
       if ((code & 3) == NODE_WALL) {
         // wall nodes: impose the lamina velocity, keep rho and f^neq
         const int rx = idx % RX, ry = idx / RX;
@@ -772,7 +773,7 @@ __device__ __forceinline__ void grid_fixed_block(
 #pragma unroll
   for (int q = 0; q < 9; ++q) own[q] = in ? f[q * N + p] : R(0);
   const int code = in ? ncode[p] : -1, typ = code & 3;
-  const GridClass<R> &cl = tab[code >= 0 ? code >> 4 : 0];
+  const GridClass<R> &cl = tab[code >= 0 ? code >> 2 : 0];
   const bool iface = code >= 0 && typ == NODE_INTERFACE;
   const int ring = idx < RN ? ring_slot<G>(gi, gj, rx, ry, nux, nuy) : -1;
 #pragma unroll
