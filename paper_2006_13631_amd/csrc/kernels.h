@@ -185,7 +185,9 @@ struct Kernels {
   static void lattice_from_grid(const CaseView<T, R> &v, const R *grid, hipStream_t s);
   static void interface_donors(const CaseView<T, R> &v, hipStream_t s);
   // one sub-step m of an unstructured grid (Eq.(ulbe), Eq.(postcollision2_u)),
-  // one node per lane; optional events at the kernel's own start and end
+  // one node per lane; sub-step 0 reads planes and the last one writes them,
+  // in between the two buffers hold the populations node by node; optional
+  // events at the kernel's own start and end
   static void mesh_substep(const CaseView<T, R> &v, const R *f, R *fout, int m, hipStream_t s,
                            hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
   // sub-steps m0 .. m0+count-1 (count <= kSubstepBlock) in one launch; with
