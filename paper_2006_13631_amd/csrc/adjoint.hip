@@ -142,17 +142,39 @@ __device__ __forceinline__ void adj_star_block(const AdjCtx<T, R> &c, int bx) {
   if (d < 3) c.M2[d * N + p] = acc[d];
 }
 
+// L consecutive lanes that serve one node: each tests one of the candidates
+// that may contribute to the node, those that do are then added in the
+// candidates' order, lane l taking the components l, l + L, ... of the sums.
+// Many lanes shorten the chain of a node, few do less work on nodes that find
+// nothing: the launchers choose by the number of nodes (refill_lanes,
+// donor_lanes, gather_lanes).
+template <int L>
+struct NodeLanes {
+  static constexpr int PER = NG / L;  // nodes per workgroup
+  // components of n each lane holds (component k: slot k / L of lane k % L)
+  static constexpr int slots(int n) { return (n + L - 1) / L; }
+  int lane, base;
+  __device__ __forceinline__ NodeLanes() : lane(threadIdx.x % L), base(threadIdx.x - threadIdx.x % L) {}
+  // the lanes of this node whose candidate contributes, one bit each
+  __device__ __forceinline__ unsigned hits(bool hit) const {
+    if constexpr (L == 1) return hit ? 1u : 0u;
+    else return (unsigned)(__ballot(hit) >> base) & (unsigned)((1ull << L) - 1);
+  }
+  template <class V>
+  __device__ __forceinline__ V from(V x, int l) const {
+    if constexpr (L == 1) return x;
+    else return __shfl(x, base + l, 64);
+  }
+};
+
 // ---- refill and force adjoint -------------------------------------------------
-// Sixteen lanes per grid node: each locates one of the new nodes that may
-// read this one (further rounds of 16 where there are more), then those that
-// do are added in their row-major order, lane k taking population k. Lane 0
-// does the rest. (One lane per node took 25 us on the 64 x 16 grid in FP64,
-// this and the star part together 10.7.)
-constexpr int kRefLanes = 16;
-template <class T, class R>
+// A lane group per grid node (NodeLanes); candidates are the new nodes that
+// may read this one, components the populations.
+template <class T, class R, int L>
 __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot0, int bx) {
-  const int q = bx * (NG / kRefLanes) + threadIdx.x / kRefLanes, sl = threadIdx.x % kRefLanes;
-  const int base = threadIdx.x - sl;
+  const NodeLanes<L> grp;
+  constexpr int S = NodeLanes<L>::slots(9);
+  const int q = bx * grp.PER + threadIdx.x / L, sl = grp.lane;
   const size_t N = (size_t)c.nnode;
   const GridGeom &g = c.gg;
   double pA = 0.0, pW = 0.0, pT = 0.0;
@@ -161,10 +183,17 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
     const int tq = c.ncode[q] & 3;
     int kind = 0;
     if (tq != NODE_WALL) kind = refill_cell(g, c.P.ybase, c.P.ybase1, i, j).kind;
-    const int s9 = sl < 9 ? sl : 0;  // population of this lane
-    const R ubs = c.Ub_next[s9 * N + q], uns = c.Un[s9 * N + q];
-    // (b) every refill that read this node of the old grid
-    R acc = (tq == NODE_WALL || kind == 2) ? ubs : R(0);
+    R ubs[S], uns[S], acc[S];  // populations sl, sl + L, ... of this lane
+    size_t at9[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int s = sl + u * L;
+      at9[u] = (size_t)(s < 9 ? s : 0) * N;
+      ubs[u] = c.Ub_next[at9[u] + q];
+      uns[u] = c.Un[at9[u] + q];
+      // (b) every refill that read this node of the old grid
+      acc[u] = (tq == NODE_WALL || kind == 2) ? ubs[u] : R(0);
+    }
     double dsum = 0.0;
     // a new node jj lands near old row jj + delta; its triangle's rows are
     // within one (two next to the lamina) of that
@@ -177,12 +206,12 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
       jlo = max((int)ceil((double)j - 2.0 - delta) - 1, 0);
       jhi = min((int)ceil((double)j + 2.0 - delta), g.nuy - 1);
     }
-    const int ilo = max(i - 1, 0), nw = min(i + 1, g.nux - 1) - ilo + 1, ncand = nw * max(jhi - jlo + 1, 0);
-    for (int c0 = 0; c0 < ncand; c0 += kRefLanes) {
-      const int cand = c0 + sl, ii = ilo + cand % nw, jj = jlo + cand / nw, pc = jj * g.nux + ii;
+    // new node (ii, jj) of this lane, then the lanes' hits in order
+    auto visit = [&](int ii, int jj, bool live) {
+      const int pc = jj * g.nux + ii;
       double lam1 = 0.0, dl1 = 0.0;
       bool hit = false;
-      if (cand < ncand && (c.ncode[pc] & 3) != NODE_WALL) {
+      if (live && (c.ncode[pc] & 3) != NODE_WALL) {
         const RefillCell r = refill_cell(g, c.P.ybase, c.P.ybase1, ii, jj);
         if (r.kind == 3) {
           int node[3];
@@ -198,16 +227,31 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
           }
         }
       }
-      unsigned hits = (unsigned)(__ballot(hit) >> base) & ((1u << kRefLanes) - 1);
+      unsigned hits = grp.hits(hit);
       while (hits) {
-        const int src = base + __builtin_ctz(hits);
+        const int src = __builtin_ctz(hits);
         hits &= hits - 1;
-        const R l = R(__shfl(lam1, src, 64));
-        const double dd = __shfl(dl1, src, 64);
-        const int ps = __shfl(pc, src, 64);
-        const R u = c.Ub_next[s9 * N + ps];
-        acc += l * u;
-        if (sl < 9) dsum += dd * ((double)u * (double)uns);
+        const R l = R(grp.from(lam1, src));
+        const double dd = grp.from(dl1, src);
+        const int ps = grp.from(pc, src);
+        double d = 0.0;
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+          const R v = c.Ub_next[at9[u] + ps];
+          acc[u] += l * v;
+          if (sl + u * L < 9) d += (double)v * (double)uns[u];
+        }
+        dsum += dd * d;
+      }
+    };
+    const int ilo = max(i - 1, 0), nw = min(i + 1, g.nux - 1) - ilo + 1, ncand = nw * max(jhi - jlo + 1, 0);
+    if constexpr (L == 1) {
+      for (int jj = jlo; jj <= jhi; ++jj)
+        for (int ii = ilo; ii < ilo + nw; ++ii) visit(ii, jj, true);
+    } else {
+      for (int c0 = 0; c0 < ncand; c0 += L) {
+        const int cand = c0 + sl;
+        visit(ilo + cand % nw, jlo + cand / nw, cand < ncand);
       }
     }
     // uniform: the new node's old-grid coordinate t = (y_{k+1} - y_k)/h + const
@@ -219,7 +263,7 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
       const double nx = c.wall_nrm[q], ny = c.wall_nrm[N + q];
       R un[9], rho, ux, uy;
 #pragma unroll
-      for (int s = 0; s < 9; ++s) un[s] = __shfl(uns, base + s, 64);
+      for (int s = 0; s < 9; ++s) un[s] = grp.from(uns[s / L], s % L);
       moments<R>(un, rho, ux, uy);
       R gb[9], fb[9];
 #pragma unroll
@@ -231,11 +275,13 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
       node_chain<R>(rho, ux, uy, rb, R(0), R(0), gb, fb);
 #pragma unroll
       for (int s = 0; s < 9; ++s)
-        if (s == sl) acc += fb[s];
+        if (s % L == sl) acc[s / L] += fb[s];
     }
-    if (sl < 9) c.Ubn[sl * N + q] = acc;
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if (sl + u * L < 9) c.Ubn[at9[u] + q] = acc[u];
     // (a) this node's own type-1 refill: adjoint of the interpolated moments
-    // (lane k writes component k; every lane computes them)
+    // (every lane computes all components and writes its own)
     R z[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) z[k] = R(0);
@@ -243,7 +289,7 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
     if (kind == 1) {
       R ub[9];
 #pragma unroll
-      for (int s = 0; s < 9; ++s) ub[s] = __shfl(ubs, base + s, 64);
+      for (int s = 0; s < 9; ++s) ub[s] = grp.from(ubs[s / L], s % L);
       R rho, ux, uy, fneq[9];
       lattice_bilinear<T, R>(c.Lt, c.nx, c.ny, c.plane, c.bc, grid_x(g, i), grid_y(g, c.P.ybase1, j), rho, ux,
                              uy, fneq);
@@ -259,7 +305,7 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
     }
 #pragma unroll
     for (int k = 0; k < 12; ++k)
-      if (k == sl) c.Z1[k * N + q] = z[k];
+      if (k % L == sl) c.Z1[k * N + q] = z[k];
     if (sl == 0) c.zf[q] = flag;
   }
   block_accum3<NG>(pA, pW, pT, c.part + 3 * (size_t)(slot0 + bx));
@@ -268,10 +314,10 @@ __device__ __forceinline__ void adj_refill_block(const AdjCtx<T, R> &c, int slot
 // The star recomputation and the refill adjoint share a launch: neither
 // reads what the other writes (star: f*, f^neq*, moments of the interface
 // nodes from the taped lattice; refill: Z1, zf, Ubn and its partial sums).
-template <class T, class R>
+template <class T, class R, int L>
 __global__ __launch_bounds__(NG) void k_adj_star_refill(AdjCtx<T, R> c, int slot0, int nstar) {
   if ((int)blockIdx.x < nstar) adj_star_block<T, R>(c, blockIdx.x);
-  else adj_refill_block<T, R>(c, slot0, (int)blockIdx.x - nstar);
+  else adj_refill_block<T, R, L>(c, slot0, (int)blockIdx.x - nstar);
 }
 
 // ---- one sub-step backwards -----------------------------------------------------
@@ -513,15 +559,15 @@ __global__ __launch_bounds__(A::NT) void k_adj_substeps(AdjCtx<T, R> c, const R 
 }
 
 // ---- donor gather: dJ/d f_pre at lattice nodes read by bilinear donors ------------
-// Half a wave per lattice node: each lane tests one candidate (grid column,
-// interface donor or type-1 refill, grid row), those that read the node are
-// added in that order, lane k taking component k of the twelve. (One lane
-// per lattice node, its candidates in turn: 13.0 us around the 64 x 16 grid
-// in FP64, this 7.5.)
-template <class T, class R>
+// A lane group per lattice node (NodeLanes): candidates are (grid column,
+// interface donor or type-1 refill, grid row) in that order, components the
+// twelve interpolated values.
+template <class T, class R, int L>
 __global__ __launch_bounds__(NG) void k_adj_donor_gather(AdjCtx<T, R> c, int slot0) {
-  const int hl = threadIdx.x & 31, half = threadIdx.x & 32;
-  const int x = c.ex0 + blockIdx.x * (NG / 32) + (threadIdx.x >> 5);
+  const NodeLanes<L> grp;
+  constexpr int S = NodeLanes<L>::slots(12);
+  const int hl = grp.lane;
+  const int x = c.ex0 + blockIdx.x * grp.PER + threadIdx.x / L;
   const int y = c.ey0 + blockIdx.y;
   const GridGeom &g = c.gg;
   const size_t N = (size_t)c.nnode;
@@ -554,20 +600,21 @@ __global__ __launch_bounds__(NG) void k_adj_donor_gather(AdjCtx<T, R> c, int slo
         nj[pos] = max(jhi - jlo[pos] + 1, 0);
       }
       const int per = nj[0] + nj[1], ncand = per * max(ihi - ilo + 1, 0);
-      R zs = R(0), zA = R(0), zW = R(0);  // component hl of the twelve
+      R zs[S], zA[S], zW[S];  // components hl, hl + L, ... of the twelve
+#pragma unroll
+      for (int u = 0; u < S; ++u) zs[u] = zA[u] = zW[u] = R(0);
       bool any = false;
-      for (int c0 = 0; c0 < ncand; c0 += 32) {
-        const int cand = c0 + hl;
+      // grid node (i, j) of this lane as interface donor (pos 0) or type-1
+      // refill (pos 1), then the lanes' hits in order
+      auto visit = [&](int i, int j, int pos, double X, int fx, bool live) {
         R wr = R(0), wa = R(0), ww = R(0);
-        int at = 0;  // 2 node + (0: interface donor, 1: type-1 refill)
+        int at = 0;  // 2 node + pos
         bool hit = false;
-        if (cand < ncand) {
-          const int i = ilo + cand / per, r = cand % per, pos = r < nj[0] ? 0 : 1;
-          const int j = pos ? jlo[1] + r - nj[0] : jlo[0] + r;
-          const int p = j * g.nux + i;
-          const double X = grid_x(g, i), Y = grid_y(g, pos ? c.P.ybase1 : c.P.ybase, j);
-          const int fx = (int)floor(X), fy = (int)floor(Y);
-          if ((fx == x || fx + 1 == x) && (fy == y || fy + 1 == y) && (c.zf[p] & (pos ? 1 : 2))) {
+        const int p = j * g.nux + i;
+        if (live && (L > 1 || (c.zf[p] & (pos ? 1 : 2)))) {
+          const double Y = grid_y(g, pos ? c.P.ybase1 : c.P.ybase, j);
+          const int fy = (int)floor(Y);
+          if ((fy == y || fy + 1 == y) && (L == 1 || (c.zf[p] & (pos ? 1 : 2)))) {
             const double dyA = pos ? c.dyA1 : c.dyA, dyW = pos ? c.dyW1 : c.dyW;
             int xd, yd;
             double w, dw;
@@ -579,28 +626,47 @@ __global__ __launch_bounds__(NG) void k_adj_donor_gather(AdjCtx<T, R> c, int slo
             hit = true;
           }
         }
-        unsigned hits = (unsigned)(__ballot(hit) >> half);
+        unsigned hits = grp.hits(hit);
         any = any || hits;
         while (hits) {
-          const int src = half + __builtin_ctz(hits);
+          const int src = __builtin_ctz(hits);
           hits &= hits - 1;
-          const R wrs = __shfl(wr, src, 64), was = __shfl(wa, src, 64), wws = __shfl(ww, src, 64);
-          const int as = __shfl(at, src, 64);
-          if (hl < 12) {
-            const R z = (as & 1 ? c.Z1 : c.Z2)[hl * N + (as >> 1)];
-            zs += wrs * z;
-            zA += was * z;
-            zW += wws * z;
+          const R wrs = grp.from(wr, src), was = grp.from(wa, src), wws = grp.from(ww, src);
+          const int as = grp.from(at, src);
+#pragma unroll
+          for (int u = 0; u < S; ++u) {
+            if (hl + u * L >= 12) continue;
+            const R z = (as & 1 ? c.Z1 : c.Z2)[(hl + u * L) * N + (as >> 1)];
+            zs[u] += wrs * z;
+            zA[u] += was * z;
+            zW[u] += wws * z;
           }
+        }
+      };
+      if constexpr (L == 1) {
+        for (int i = ilo; i <= ihi; ++i) {
+          const double X = grid_x(g, i);
+          const int fx = (int)floor(X);
+          if (fx != x && fx + 1 != x) continue;
+          for (int pos = 0; pos < 2; ++pos)
+            for (int r = 0; r < nj[pos]; ++r) visit(i, jlo[pos] + r, pos, X, fx, true);
+        }
+      } else {
+        for (int c0 = 0; c0 < ncand; c0 += L) {
+          const int cand = c0 + hl, i = ilo + cand / per, r = cand % per, pos = r < nj[0] ? 0 : 1;
+          const double X = cand < ncand ? grid_x(g, i) : 0.0;
+          const int fx = (int)floor(X);
+          visit(i, pos ? jlo[1] + r - nj[0] : jlo[0] + r, pos, X, fx,
+                cand < ncand && (fx == x || fx + 1 == x));
         }
       }
       if (any) {
         R f[9], e[9], rho, ux, uy, fneq[9], z[12], za[12], zw[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-          z[k] = __shfl(zs, half + k, 64);
-          za[k] = __shfl(zA, half + k, 64);
-          zw[k] = __shfl(zW, half + k, 64);
+          z[k] = grp.from(zs[k / L], k % L);
+          za[k] = grp.from(zA[k / L], k % L);
+          zw[k] = grp.from(zW[k / L], k % L);
         }
         pull<T, R>(c.Lt, c.nx, c.ny, c.plane, c.bc, x, y, f);
         moments<R>(f, rho, ux, uy);
@@ -617,7 +683,7 @@ __global__ __launch_bounds__(NG) void k_adj_donor_gather(AdjCtx<T, R> c, int slo
     const size_t plane = (size_t)c.ew * c.eh, at = (size_t)(y - c.ey0) * c.ew + (x - c.ex0);
 #pragma unroll
     for (int k = 0; k < 9; ++k)
-      if (k == hl) c.E[k * plane + at] = Eo[k];
+      if (k % L == hl) c.E[k * plane + at] = Eo[k];
   }
   block_accum3<NG>(pA, pW, 0.0, c.part + 3 * (size_t)(slot0 + blockIdx.y * gridDim.x + blockIdx.x));
 }
@@ -771,15 +837,15 @@ __global__ __launch_bounds__(NT) void k_adj_from_grid(AdjCtx<T, R> c, int slot0)
 }
 
 // ---- grid-to-lattice adjoint, grid side -------------------------------------------
-// Half a wave per grid node. Each lane locates one candidate lattice node in
-// the grid (those around the node: up to 5 x 5 on a unit grid; further
-// rounds of 32 where the spacing is wider); the candidates whose triangle
-// holds the grid node are then added in their row-major order, lane k taking
-// component k of the twelve. (One lane per grid node locating its
-// candidates in turn took 39 us on the 64 x 16 grid in FP64, this 8.1.)
-template <class T, class R>
+// A lane group per grid node (NodeLanes): candidates are the lattice nodes
+// around it (up to 5 x 5 on a unit grid), which their lane locates in the
+// grid; those whose triangle holds the grid node contribute their twelve
+// interpolated values.
+template <class T, class R, int L>
 __global__ __launch_bounds__(NG) void k_adj_from_grid_gather(AdjCtx<T, R> c, R *__restrict__ ub, int slot0) {
-  const int q = blockIdx.x * (NG / 32) + (threadIdx.x >> 5), hl = threadIdx.x & 31, half = threadIdx.x & 32;
+  const NodeLanes<L> grp;
+  constexpr int S = NodeLanes<L>::slots(12);
+  const int q = blockIdx.x * grp.PER + threadIdx.x / L, hl = grp.lane;
   const GridGeom &g = c.gg;
   const size_t N = (size_t)c.nnode;
   double pA = 0.0, pW = 0.0;
@@ -812,10 +878,12 @@ __global__ __launch_bounds__(NG) void k_adj_from_grid_gather(AdjCtx<T, R> c, R *
     const bool away = xhi < min(P.ix0, P.pix0) || xlo > max(P.ix1, P.pix1) || yhi < min(P.iy0, P.piy0) ||
                       ylo > max(P.iy1, P.piy1);
     const int nw = xhi - xlo + 1, ncand = (deep || away || nw < 1) ? 0 : nw * max(yhi - ylo + 1, 0);
-    R zs = R(0), zd = R(0);  // component hl of the twelve
+    R zs[S], zd[S];  // components hl, hl + L, ... of the twelve
+#pragma unroll
+    for (int u = 0; u < S; ++u) zs[u] = zd[u] = R(0);
     bool any = false;
     const size_t zp = (size_t)c.k2_w * c.k2_h;
-    for (int c0 = 0; c0 < ncand; c0 += 32) {
+    for (int c0 = 0; c0 < ncand; c0 += L) {
       const int cand = c0 + hl;
       const int xl = xlo + cand % nw, yl = ylo + cand / nw;
       R l = R(0), d = R(0);
@@ -836,17 +904,19 @@ __global__ __launch_bounds__(NG) void k_adj_from_grid_gather(AdjCtx<T, R> c, R *
           hit = true;
         }
       }
-      unsigned hits = (unsigned)(__ballot(hit) >> half);
+      unsigned hits = grp.hits(hit);
       any = any || hits;
       while (hits) {
-        const int src = half + __builtin_ctz(hits);
+        const int src = __builtin_ctz(hits);
         hits &= hits - 1;
-        const R ls = __shfl(l, src, 64), ds = __shfl(d, src, 64);
-        const int as = __shfl(at, src, 64);
-        if (hl < 12) {
-          const R z = c.Z3[hl * zp + as];
-          zs += ls * z;
-          zd += ds * z;
+        const R ls = grp.from(l, src), ds = grp.from(d, src);
+        const int as = grp.from(at, src);
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+          if (hl + u * L >= 12) continue;
+          const R z = c.Z3[(hl + u * L) * zp + as];
+          zs[u] += ls * z;
+          zd[u] += ds * z;
         }
       }
     }
@@ -854,8 +924,8 @@ __global__ __launch_bounds__(NG) void k_adj_from_grid_gather(AdjCtx<T, R> c, R *
       R f[9], e[9], rho, ux, uy, fneq[9], fb[9], z[12], zdv[12];
 #pragma unroll
       for (int k = 0; k < 12; ++k) {
-        z[k] = __shfl(zs, half + k, 64);
-        zdv[k] = __shfl(zd, half + k, 64);
+        z[k] = grp.from(zs[k / L], k % L);
+        zdv[k] = grp.from(zd[k / L], k % L);
       }
 #pragma unroll
       for (int k = 0; k < 9; ++k) f[k] = c.U0[k * N + q];
@@ -898,54 +968,103 @@ __global__ void k_set_counter(int64_t *dk, int64_t k) { *dk = k; }
 
 }  // namespace
 
+// Lanes per node of the gathers. A node that finds something is a chain of
+// dependent locations and loads, which more lanes shorten; one that finds
+// nothing (most of them on a large grid) costs its group all the same. us a
+// launch in FP64 (FP32 within a fifth), by grid:
+//                          64x16  256x64  384x96  512x128  1024x256
+//   star and refill  16     10.1    18.5    30.0     46.8     172
+//                     4     12.8    14.4    17.5     29.0      82
+//                     1     25.9    24.5    27.4     27.1      56
+//   donors           32      7.6    12.8    19.0     26.8      93
+//                    16      8.2    11.0    14.4     18.7      53
+//                     1     12.6    12.0    11.8     12.2      18
+//   grid to lattice  32      8.1    12.2    18.8     25.8      67
+//                    16      8.5    12.2    15.2     20.4      46
+//                     1     37.5    33.4    33.5     36.6      52
+int refill_lanes(int nnode) { return nnode <= 8192 ? 16 : nnode <= 49152 ? 4 : 1; }
+int donor_lanes(int ew, int eh) {
+  const int64_t n = (int64_t)ew * eh;
+  return n <= 4096 ? 32 : n <= 24576 ? 16 : 1;
+}
+int gather_lanes(int nnode) { return nnode <= 2048 ? 32 : 16; }
+
+// Tile of the reverse sub-steps: 8 x 8 in FP64, where the 576 lanes of a
+// 16 x 16 tile leave too few registers for a node's weights (162 of them go
+// to memory) and a compute unit holds one workgroup. In FP32 8 x 8 while the
+// grid's tiles fit the compute units twice over (a sub-step of four waves is
+// the shortest), then 16 x 16, which spends less on halos (44 % of the lanes
+// own a node, against 25). us of a launch of four, 8 x 8 and 16 x 16: 256 x 64
+// grid 16.3 and 52.0 in FP64, 14.2 and 16.3 in FP32; 384 x 96 35.3, 65.9 and
+// 23.5, 17.2; 512 x 128 56.0, 76.7 and 28.3, 18.5; 1024 x 256 183, 293 and
+// 87, 63.
+template <class A>
+int adj_tiles(int nux, int nuy) {
+  return ((nux + A::TX - 1) / A::TX) * ((nuy + A::TY - 1) / A::TY);
+}
+template <class R, class F>
+void with_tile(int nux, int nuy, F f) {
+  if constexpr (sizeof(R) == 4) {
+    if (adj_tiles<AdjSmall>(nux, nuy) > 512) return f(AdjLarge{});
+  }
+  f(AdjSmall{});
+}
+
+// A launcher's choice of lanes per node, as a compile-time constant: the
+// first of the list that equals it.
+template <int L, int... More, class F>
+void with_lanes(int lanes, F f) {
+  if constexpr (sizeof...(More) > 0) {
+    if (lanes != L) return with_lanes<More...>(lanes, f);
+  }
+  f(std::integral_constant<int, L>{});
+}
+
 template <class T, class R>
 void AdjKernels<T, R>::star_refill(const AdjCtx<T, R> &c, int slot0, hipStream_t s) {
   const int nstar = (int)blocks((size_t)4 * c.n_iface, NG);
-  hipLaunchKernelGGL((k_adj_star_refill<T, R>), dim3(nstar + refill_slots(c)), dim3(NG), 0, s, c, slot0, nstar);
+  with_lanes<16, 4, 1>(refill_lanes(c.nnode), [&](auto L) {
+    hipLaunchKernelGGL((k_adj_star_refill<T, R, L>), dim3(nstar + refill_slots(c)), dim3(NG), 0, s, c, slot0, nstar);
+  });
 }
 
 template <class T, class R>
 int AdjKernels<T, R>::refill_slots(const AdjCtx<T, R> &c) {
-  return (int)blocks(c.nnode, NG / kRefLanes);
+  return (int)blocks(c.nnode, NG / refill_lanes(c.nnode));
 }
 
-// 8 x 8 tiles while the grid's fit the compute units twice over: a sub-step of
-// four waves is the shortest; larger grids take 16 x 16, which spend less on
-// halos (44 % of the lanes own a node, against 25)
-static int adj_tiles(int nux, int nuy, int tx, int ty) { return ((nux + tx - 1) / tx) * ((nuy + ty - 1) / ty); }
-static bool adj_small(int nux, int nuy) {
-  return adj_tiles(nux, nuy, AdjSmall::TX, AdjSmall::TY) <= 512;
-}
 template <class T, class R>
 int AdjKernels<T, R>::substep_slots(const AdjCtx<T, R> &c) {
-  return adj_small(c.gg.nux, c.gg.nuy) ? adj_tiles(c.gg.nux, c.gg.nuy, AdjSmall::TX, AdjSmall::TY)
-                                       : adj_tiles(c.gg.nux, c.gg.nuy, AdjLarge::TX, AdjLarge::TY);
+  int n = 0;
+  with_tile<R>(c.gg.nux, c.gg.nuy, [&](auto tile) { n = adj_tiles<decltype(tile)>(c.gg.nux, c.gg.nuy); });
+  return n;
 }
 template <class T, class R>
 void AdjKernels<T, R>::substeps(const AdjCtx<T, R> &c, const R *tape0, const R *ub, R *ub_out, int m_hi, int count,
                                 const AdjSubScal<R> &sc, int first, int last, int slot0, hipStream_t s,
                                 hipEvent_t start, hipEvent_t stop) {
-  const dim3 grid(substep_slots(c));
-  auto launch = [&](auto tile) {
+  with_tile<R>(c.gg.nux, c.gg.nuy, [&](auto tile) {
     using A = decltype(tile);
+    const dim3 grid(adj_tiles<A>(c.gg.nux, c.gg.nuy));
     if (start || stop)
       hipExtLaunchKernelGGL((k_adj_substeps<T, R, A>), grid, dim3(A::NT), 0, s, start, stop, 0, c, tape0, ub, ub_out,
                             m_hi, count, sc, first, last, slot0);
     else
       hipLaunchKernelGGL((k_adj_substeps<T, R, A>), grid, dim3(A::NT), 0, s, c, tape0, ub, ub_out, m_hi, count, sc,
                          first, last, slot0);
-  };
-  if (adj_small(c.gg.nux, c.gg.nuy)) launch(AdjSmall{});
-  else launch(AdjLarge{});
+  });
 }
 
 template <class T, class R>
 int AdjKernels<T, R>::donor_gather_slots(const AdjCtx<T, R> &c) {
-  return (int)blocks(c.ew, NG / 32) * c.eh;
+  return (int)blocks(c.ew, NG / donor_lanes(c.ew, c.eh)) * c.eh;
 }
 template <class T, class R>
 void AdjKernels<T, R>::donor_gather(const AdjCtx<T, R> &c, int slot0, hipStream_t s) {
-  hipLaunchKernelGGL((k_adj_donor_gather<T, R>), dim3(blocks(c.ew, NG / 32), c.eh), dim3(NG), 0, s, c, slot0);
+  const dim3 grid(blocks(c.ew, NG / donor_lanes(c.ew, c.eh)), c.eh);
+  with_lanes<32, 16, 1>(donor_lanes(c.ew, c.eh), [&](auto L) {
+    hipLaunchKernelGGL((k_adj_donor_gather<T, R, L>), grid, dim3(NG), 0, s, c, slot0);
+  });
 }
 
 template <class T, class R>
@@ -975,11 +1094,14 @@ void AdjKernels<T, R>::from_grid(const AdjCtx<T, R> &c, int slot0, hipStream_t s
 
 template <class T, class R>
 int AdjKernels<T, R>::from_grid_gather_slots(const AdjCtx<T, R> &c) {
-  return (int)blocks(c.nnode, NG / 32);
+  return (int)blocks(c.nnode, NG / gather_lanes(c.nnode));
 }
 template <class T, class R>
 void AdjKernels<T, R>::from_grid_gather(const AdjCtx<T, R> &c, R *ub, int slot0, hipStream_t s) {
-  hipLaunchKernelGGL((k_adj_from_grid_gather<T, R>), dim3(from_grid_gather_slots(c)), dim3(NG), 0, s, c, ub, slot0);
+  with_lanes<32, 16>(gather_lanes(c.nnode), [&](auto L) {
+    hipLaunchKernelGGL((k_adj_from_grid_gather<T, R, L>), dim3(from_grid_gather_slots(c)), dim3(NG), 0, s, c, ub,
+                       slot0);
+  });
 }
 
 void adj_reduce(const double *part, int nslots, double *out, hipStream_t s) {
