@@ -516,8 +516,8 @@ class Case final : public CaseBase {
       Kernels<T, R>::advance_step(v, s_grid_);
     } else if (timing_ != 1) {  // one launch (level 1 times the two apart)
       if (!next_fits_ || s_grid_ != s_main_) next = nullptr;
-      Kernels<T, R>::refill_force(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], done_, outside_rows_, s_grid_, next,
-                                  next_targets_);
+      Kernels<T, R>::refill_force(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], done_, outside_rows_, face_rows_, s_grid_,
+                                  next, next_targets_);
       next_done_ = next != nullptr;
     } else {
       Kernels<T, R>::refill(v, (const R *)gbuf_[cur], (R *)gbuf_[1 - cur], s_grid_);
@@ -1523,12 +1523,15 @@ class Case final : public CaseBase {
     return true;
   }
 
-  // Sizes of the refill launch: the rows at either end of the grid that a
-  // step's motion may take out of its old extent, the largest number of
-  // lattice interpolation nodes of a step (the rectangle's perimeter and the
-  // rows it uncovered), and whether the refill may write those of the next
-  // step: every node of a triangle that can hold one (2 or more inside the
-  // grid's edge) must lie farther from the edge than a step moves.
+  // Sizes of the refill launch: the rows whose nodes may be of type 1 (at
+  // either end of the grid those that a step's motion may take out of its old
+  // extent, on either side of the lamina those that it may take onto its old
+  // face, where rounding decides between the slot's cells and the cell beside
+  // them), the largest number of lattice interpolation nodes of a step (the
+  // rectangle's perimeter and the rows it uncovered), and whether the refill
+  // may write those of the next step: no node of a triangle that can hold one
+  // (less than kMargin + 1 inside the grid's edge, and the triangle's own
+  // size) may be of type 1.
   void plan_refill() {
     const double dmax = std::fabs(d_.A * d_.omega) + 1e-6;  // no step moves farther than the greatest speed
     const StepParams &S = P_host_[0];
@@ -1550,6 +1553,17 @@ class Case final : public CaseBase {
       for (int j = 0; j + 1 < ny; ++j)
         if (dist(j + 1, up) > kMargin - 1e-6 && dist(j, up) < dmax) next_fits_ = false;
     }
+    face_rows_ = 0;
+    if (!body_) return;
+    const int face = ny / 2 - 1;  // the row of the lower face (the rows are symmetric)
+    while (face_rows_ < face - outside_rows_ && dist(face, 0) - dist(face - 1 - face_rows_, 0) < dmax) ++face_rows_;
+    if (face_rows_ == 0) return;
+    double cx = h_, cy = h_;  // the largest cell
+    for (size_t i = 1; i < gx_.size(); ++i) cx = std::max(cx, gx_[i] - gx_[i - 1]);
+    for (size_t j = 1; j < gy_.size(); ++j) cy = std::max(cy, gy_[j] - gy_[j - 1]);
+    if (std::min(-gex0_, gex1_) - kMargin - 1.0 - cx < 0.5 * cfg_.b + 1e-6 ||
+        gey1_ - kMargin - 1.0 - cy < 0.5 * cfg_.thickness + dmax)
+      next_fits_ = false;
   }
 
   StepParams params_at(int64_t k) const {
@@ -2093,6 +2107,7 @@ class Case final : public CaseBase {
   int timing_ = 0;  // 1: every kernel, 2: the stream-collide only
   double *stage_ = nullptr;  // device staging of state reads (read_lattice)
   int outside_rows_ = 0;    // grid rows at either end a step may move out of the old grid
+  int face_rows_ = 0;       // grid rows on either side of the lamina a step may move onto its old face
   bool next_fits_ = false;  // the refill may write the next step's interpolation nodes
   int next_targets_ = 0;    // most lattice interpolation nodes of any step
   bool next_done_ = false;  // the next step's are written already (never between calls)

@@ -210,13 +210,15 @@ struct Kernels {
   // refill and force (prescribed motion) in one launch, then the step
   // counter advances; done: a device counter that starts at 0 and is left at
   // 0; outside_rows: grid rows at either end whose nodes the motion may take
-  // out of the old grid (split-quad grids); next (optional, split-quad
+  // out of the old grid, face_rows: rows on either side of the lamina that it
+  // may take onto the lamina's old face (split-quad grids: no other row may
+  // hold a type 1 node); next (optional, split-quad
   // grids): the lattice of t_{k+1}, complete and read by no one else during
   // the launch, which also gets the interpolation nodes of step k + 1 (at
   // most `targets` of them), as lattice_from_grid would write them from the
-  // refilled grid; no corner of their triangles may move out of the old grid
+  // refilled grid; no corner of their triangles may be of type 1
   static void refill_force(const CaseView<T, R> &v, const R *fold, R *fnew, unsigned *done, int outside_rows,
-                           hipStream_t s, T *next = nullptr, int targets = 0);
+                           int face_rows, hipStream_t s, T *next = nullptr, int targets = 0);
   // advance = 0: leave the step counter (a coupled-motion step then runs the
   // refill and advance_step after it)
   static void force(const CaseView<T, R> &v, const R *f, hipStream_t s, int advance = 1);

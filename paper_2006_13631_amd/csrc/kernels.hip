@@ -1281,16 +1281,22 @@ __device__ __forceinline__ void refill_block(const CaseView<T, R> &v, const T *_
 }
 
 // The type 1 nodes of a split-quad grid: a node the grid moves out of its old
-// extent, so one of the n1 lowest or highest rows. Four consecutive lanes
-// take the four bilinear donors of one node (one round trip of loads in
-// place of four) and each sums them in the order of lattice_bilinear.
+// extent, so one of the n1 lowest or highest rows, or one that lands on the
+// lamina's old face (refill_cell may then see it in the slot's cells and yet
+// not inside the lamina), so one of the nf rows beside either face. Four
+// consecutive lanes take the four bilinear donors of one node (one round trip
+// of loads in place of four) and each sums them in the order of
+// lattice_bilinear.
 template <class T, class R>
 __device__ __forceinline__ void outside_block(const CaseView<T, R> &v, const T *__restrict__ A, R *__restrict__ fn,
-                                              int64_t k, int n1, int bx) {
+                                              int64_t k, int n1, int nf, int bx) {
   const int gt = bx * blockDim.x + threadIdx.x, t = gt >> 2, d = gt & 3;
-  const int i = t % v.nux, r = t / v.nux, j = r < n1 ? r : v.nuy - 2 * n1 + r, p = j * v.nux + i;
+  const int i = t % v.nux, r = t / v.nux, rf = r - 2 * n1;
+  // the lowest rows, the highest, those below the lamina, those above
+  const int j = r < n1 ? r : rf < 0 ? v.nuy + rf : rf < nf ? v.nuy / 2 - 1 - nf + rf : v.nuy / 2 + 1 + rf - nf;
+  const int p = j * v.nux + i;
   const StepParams &P = v.params[k];
-  bool valid = r < 2 * n1 && (v.ncode[p] & 3) != NODE_WALL;
+  bool valid = r < 2 * (n1 + nf) && (v.ncode[p] & 3) != NODE_WALL;
   R acc[12];
 #pragma unroll
   for (int c = 0; c < 12; ++c) acc[c] = R(0);
@@ -1573,7 +1579,7 @@ __global__ __launch_bounds__(256) void k_force(const R *__restrict__ f, const Wa
 // advanced step.
 template <class T, class R, int GRID>
 __global__ __launch_bounds__(256) void k_refill_force(CaseView<T, R> vv, const R *__restrict__ fo,
-                                                      R *__restrict__ fn, unsigned *done, int n1, int nout,
+                                                      R *__restrict__ fn, unsigned *done, int n1, int nf, int nout,
                                                       T *__restrict__ next, int nnext) {
   CaseView<T, R> v = vv;
   if (GRID == 0) v.gx = v.gy = nullptr;
@@ -1584,7 +1590,7 @@ __global__ __launch_bounds__(256) void k_refill_force(CaseView<T, R> vv, const R
     force_block<R>(fo, v.wall, v.n_wall_edges, v.nnode, v.dk, v.hist, v.flag, MotionCtx{}, nullptr, nullptr, 0,
                    0);
   else if (GRID != 2 && b < nout)
-    outside_block<T, R>(v, v.A, fn, k, n1, b);
+    outside_block<T, R>(v, v.A, fn, k, n1, nf, b);
   else if (GRID != 2 && b < nout + nnext)
     next_from_grid_block<T, R>(v, next, fo, k, b - nout);
   else
@@ -2026,12 +2032,13 @@ void Kernels<T, R>::force(const CaseView<T, R> &v, const R *f, hipStream_t s, in
 
 template <class T, class R>
 void Kernels<T, R>::refill_force(const CaseView<T, R> &v, const R *fold, R *fnew, unsigned *done, int outside_rows,
-                                 hipStream_t s, T *next, int targets) {
+                                 int face_rows, hipStream_t s, T *next, int targets) {
   const int nref = (int)blocks(v.nnode, 256), nnext = next ? (int)blocks((size_t)4 * targets, 256) : 0;
-  const int nout = v.mesh ? 0 : (int)blocks((size_t)8 * outside_rows * v.nux, 256);
+  const int nout = v.mesh ? 0 : (int)blocks((size_t)8 * (outside_rows + face_rows) * v.nux, 256);
   const dim3 g(1 + nout + nnext + nref);
-#define HLBM_RF(GRID) \
-  hipLaunchKernelGGL((k_refill_force<T, R, GRID>), g, dim3(256), 0, s, v, fold, fnew, done, outside_rows, nout, next, nnext)
+#define HLBM_RF(GRID)                                                                                    \
+  hipLaunchKernelGGL((k_refill_force<T, R, GRID>), g, dim3(256), 0, s, v, fold, fnew, done, outside_rows, \
+                     face_rows, nout, next, nnext)
   if (v.mesh) HLBM_RF(2);
   else if (v.gx) HLBM_RF(1);
   else HLBM_RF(0);
