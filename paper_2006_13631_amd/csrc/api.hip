@@ -529,6 +529,12 @@ class Case final : public CaseBase {
     return e;
   }
 
+  // Steps enqueued from here on start from the state as it stands: a run (or
+  // a capture) that an error ended may have left the next step's lattice
+  // nodes marked as written, by a launch whose step does not count or that
+  // never ran.
+  void begin_run() { next_done_ = false; }
+
   // lattice interpolation nodes of the step, unless the previous step's
   // refill wrote them
   void from_grid(const CaseView<T, R> &v) {
@@ -605,6 +611,7 @@ class Case final : public CaseBase {
   // otherwise (and for an odd last step)
   hipError_t enqueue_steps(int n, int *done) {
     *done = 0;
+    begin_run();
     while (*done < n) {
       hipError_t e;
       if (two_step_ && timing_ != 1 && n - *done >= 2) {
@@ -1699,6 +1706,7 @@ class Case final : public CaseBase {
   void *lattice_buffer(int i) const { return lat_[i]; }  // 0: state at t_k, 1: at t_{k-1}
   size_t plane() const { return plane_; }
   bool has_grid() const { return has_grid_; }
+  // one step of a run that begin_run opened
   hipError_t enqueue_one(bool more) { return enqueue_step(more); }
   struct Layout {
     void *l0, *l1, *l2;
@@ -2110,7 +2118,7 @@ class Case final : public CaseBase {
   int face_rows_ = 0;       // grid rows on either side of the lamina a step may move onto its old face
   bool next_fits_ = false;  // the refill may write the next step's interpolation nodes
   int next_targets_ = 0;    // most lattice interpolation nodes of any step
-  bool next_done_ = false;  // the next step's are written already (never between calls)
+  bool next_done_ = false;  // the next step's are written already (within a run only: begin_run)
   int substep_variant_ = -1;  // grid sub-step kernel variant (-1: the default for R)
   int lattice_threads_ = kLatticeThreads, lattice_rows_ = kLatticeRows;  // stream-collide launch shape
   int lattice_order_ = 0;  // 1: stream-collide rows banded by XCD
@@ -2850,7 +2858,7 @@ class MultiLevel final : public CaseBase {
         std::swap(lev_[0].m[0], lev_[0].m[1]);
         fine_->advance_host(per);
       } else {
-        HIPCHK(advance(0));
+        HIPCHK(run_step());
       }
     }
     HIPCHK(hipStreamSynchronize(s_));
@@ -3008,6 +3016,12 @@ class MultiLevel final : public CaseBase {
     }
   }
 
+  // enqueue one step of level 0, a run of its own
+  hipError_t run_step() {
+    fine_->begin_run();
+    return advance(0);
+  }
+
   // enqueue one step of level l (and 2^(l'-l) of every finer level l');
   // more: further steps of the finest level follow in the same run
   hipError_t advance(int l, bool more = false) {
@@ -3049,7 +3063,7 @@ class MultiLevel final : public CaseBase {
     const auto fl = fine_->layout();
     hipError_t e = hipStreamBeginCapture(s_, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
-    const hipError_t e2 = advance(0);
+    const hipError_t e2 = run_step();
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(s_, &g);
     for (int l = 0; l < L_ - 1; ++l) lev_[l] = saved[l];
