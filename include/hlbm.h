@@ -146,8 +146,16 @@ typedef struct hlbm_tuning {
                               5: 16x8, 128; 6: 16x16, 256; 7: 8x4, 64
                               (4-7: several nodes per lane, more workgroups
                               per CU), each up to 4 sub-steps per launch;
-                              single case only: 8: 32x8, 384, one sub-step
-                              per launch; 9: 24x8, 512; 10: 32x8, 448, two */
+                              single case only: 8: 32x8, 256, one sub-step
+                              per launch; 9: 24x8, 512; 10: 32x8, 448, two.
+                              The large tiles give way on small grids: 0 to
+                              3 while the running grids hold at most 320
+                              such tiles, 3 to 2 while at most 160. (0, 2,
+                              3 and 9 once named 16x16, 64x4, 16x8 and a
+                              16x16 tile of one sub-step per launch: a
+                              stored schedule stays valid, gives the same
+                              bits and is no slower, but runs other
+                              kernels; hlbm_tune finds the current best) */
   int32_t order;           /* batch work lists: 0 case by case, 1 dealt to
                               the 8 XCDs in contiguous chunks; single
                               case: bit 0 gives each XCD a contiguous band

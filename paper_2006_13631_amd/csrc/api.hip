@@ -2553,7 +2553,14 @@ class Batch final : public CaseBase {
   // the sub-step kernel for this set of running cases
   int variant_for(const std::vector<int> &act) const {
     const int sv = (tuning_.tail_variant >= 0 && is_tail(act)) ? tuning_.tail_variant : tuning_.substep_variant;
-    return sv < 0 ? kBatchSubstepVariant : sv;
+    return fitted_substep_variant(sv < 0 ? kBatchSubstepVariant : sv, [&](int s) {
+      int64_t n = 0;
+      for (int c : act) {
+        const CaseView<T, R> v = cases_[c]->batched_view();
+        n += substep_tiles(s, v.nux, v.nuy);
+      }
+      return n;
+    });
   }
 
   bool persistent_for(const std::vector<int> &act) const {

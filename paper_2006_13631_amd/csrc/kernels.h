@@ -143,9 +143,10 @@ constexpr int kTwoStepTX = 64, kTwoStepTY = 8;
 //   6: 16 x 16, 256 threads   7: 8 x 4, 64 threads
 // (4-7: several nodes per lane, more workgroups per CU), each advancing up to
 // kSubstepBlock sub-steps per launch; single cases also take
-//   8: 32 x 8, 384 threads, one sub-step per launch
+//   8: 32 x 8, 256 threads, one sub-step per launch
 //   9: 24 x 8, 512 threads
 //  10: 32 x 8, 448 threads, two sub-steps per launch
+// 0 and 3 stand for the next smaller tile on few tiles: fitted_substep_variant
 constexpr int kSubstepVariants = 8;         // case-batched kernels
 constexpr int kSubstepVariantsSingle = 11;  // single-case kernels
 // sub-steps a launch of `variant` advances at most (callers step by it)
@@ -155,11 +156,36 @@ int substep_block(int variant);
 // compute units.
 template <class R>
 int default_substep_variant(int nux, int nuy);
-// ... and a batch: of 16 lattices of 256^2 to 1024^2 308 us per step in FP32
-// and 491 in FP64 (32 x 8 tiles 347 and 545), of 12 of 320^2 439 in FP64 (432)
+// ... and a batch (fitted_substep_variant then): of 16 lattices of 256^2 to
+// 1024^2 282 us per step in FP32 and 452 in FP64 (32 x 8 tiles 305 and 479), of
+// 12 of 320^2 with a 160 x 40 grid 92 and 123 (110 and 151)
 constexpr int kBatchSubstepVariant = 3;
 // tile shape of a sub-step variant (work lists of the batched kernel)
 void substep_tile(int variant, int *tx, int *ty);
+// The variant that runs where `variant` is asked for: the large tiles 0 and 3
+// leave most compute units idle while the grids hold few of them, so few 0
+// give way to 3, and few 3 to 2. tiles(v): tiles of variant v in all grids of
+// the launch. us per step, by 24 x 16 tiles, with these and with 8 x 8 tiles:
+// 84 (four 160 x 40 grids) 94.4 and 84.2 in FP64, 69.8 and 61.0 in FP32; 84
+// (one 333 x 90) 55.1, 44.5 and 40.7, 34.5; 144 (twelve 128 x 32) 560, 440 and
+// 398, 323; 176 (512 x 128) 59.9, 70.6 and 43.8, 46.4; 252 (twelve 160 x 40)
+// 123, 145 and 92, 105. By 32 x 16 tiles, with these and with 24 x 16: 128
+// (512 x 128) 67.3, 59.9 and 48.1, 43.8; 192 (six 256 x 64) 357, 298 and 233,
+// 220; 320 (forty 128 x 32) 248, 217 and 157, 148; 512 (1024 x 256) 125, 134
+// and 90, 94.
+constexpr int kFewTiles0 = 320, kFewTiles3 = 160;
+template <class Tiles>
+int fitted_substep_variant(int variant, Tiles tiles) {
+  if (variant == 0 && tiles(0) <= kFewTiles0) variant = 3;
+  if (variant == 3 && tiles(3) <= kFewTiles3) variant = 2;
+  return variant;
+}
+// tiles of a sub-step variant in one grid
+inline int64_t substep_tiles(int variant, int nux, int nuy) {
+  int tx, ty;
+  substep_tile(variant, &tx, &ty);
+  return (int64_t)((nux + tx - 1) / tx) * ((nuy + ty - 1) / ty);
+}
 
 template <class T, class R>
 struct Kernels {

@@ -926,7 +926,7 @@ template <> struct SubstepVariant<4> : SubstepShape<8, 8, 64> {};
 template <> struct SubstepVariant<5> : SubstepShape<16, 8, 128> {};
 template <> struct SubstepVariant<6> : SubstepShape<16, 16, 256> {};
 template <> struct SubstepVariant<7> : SubstepShape<8, 4, 64> {};
-template <> struct SubstepVariant<8> : SubstepShape<32, 8, 384, 1> {};
+template <> struct SubstepVariant<8> : SubstepShape<32, 8, 256, 1> {};
 template <> struct SubstepVariant<9> : SubstepShape<24, 8, 512> {};
 template <> struct SubstepVariant<10> : SubstepShape<32, 8, 448, 2> {};
 
@@ -1855,9 +1855,7 @@ int default_substep_variant(int nux, int nuy) {
   int best = 1;
   double best_us = 0.0;
   for (int i = 0; i < nc; ++i) {
-    int tx, ty;
-    substep_tile(c[i].v, &tx, &ty);
-    const int64_t tiles = (int64_t)((nux + tx - 1) / tx) * ((nuy + ty - 1) / ty);
+    const int64_t tiles = substep_tiles(c[i].v, nux, nuy);
     const double us = c[i].us * (double)((tiles + (int64_t)cus * c[i].res - 1) / ((int64_t)cus * c[i].res));
     if (i == 0 || us < best_us) {
       best = c[i].v;
@@ -2004,7 +2002,9 @@ template <class T, class R>
 void Kernels<T, R>::grid_substeps(const CaseView<T, R> &v, const R *f, R *fout, int m0, int count, hipStream_t s,
                                   R *tape, R *wtape, const int *widx, int nwall, int variant, hipEvent_t start,
                                   hipEvent_t stop) {
-  switch (variant < 0 ? default_substep_variant<R>(v.nux, v.nuy) : variant) {
+  variant = variant < 0 ? default_substep_variant<R>(v.nux, v.nuy)
+                        : fitted_substep_variant(variant, [&](int s) { return substep_tiles(s, v.nux, v.nuy); });
+  switch (variant) {
 #define HLBM_V(V) \
   case V: grid_substeps_v<V>(v, f, fout, m0, count, s, tape, wtape, widx, nwall, start, stop); break;
     HLBM_V(1) HLBM_V(2) HLBM_V(3) HLBM_V(4) HLBM_V(5) HLBM_V(6) HLBM_V(7) HLBM_V(8) HLBM_V(9) HLBM_V(10)
