@@ -949,10 +949,14 @@ __global__ __launch_bounds__(SubstepVariant<V>::NT) void k_grid_substeps(
         widx, nwall);
 }
 
-// launch m0 / kSubstepBlock of a batched step: item = (case, tile)
+// launch m0 / kSubstepBlock of a batched step: item = (case, tile). Variant 6
+// in FP64 is told that no more than two waves share a SIMD (its LDS allows no
+// more), or it is scheduled for fewer registers: sixteen lattices of 256^2 to
+// 1024^2 486 us per step without, 470 with.
 template <class T, class R, int V>
-__global__ __launch_bounds__(SubstepVariant<V>::NT) void kb_grid_substeps(const CaseView<T, R> *__restrict__ views,
-                                                                          const int4 *__restrict__ items, int m0) {
+__global__ __launch_bounds__(SubstepVariant<V>::NT)
+__attribute__((amdgpu_waves_per_eu(1, V == 6 && sizeof(R) == 8 ? 2 : 8))) void kb_grid_substeps(
+    const CaseView<T, R> *__restrict__ views, const int4 *__restrict__ items, int m0) {
   using SV = SubstepVariant<V>;
   const int4 it = items[blockIdx.x];
   const CaseView<T, R> &v = views[it.x];
