@@ -176,7 +176,8 @@ typedef struct hlbm_tuning {
                               per lane; single case: 0                     */
   int32_t persistent_groups; /* batch: workgroups of the cooperative launch
                               (0: as many as the widest kernel of a step
-                              has work items, at most what fits at once)   */
+                              has work items, at most 1024); always at most
+                              what fits at once                            */
   double ms_per_step;      /* measured for the chosen schedule (output)      */
 } hlbm_tuning;
 
