@@ -12,22 +12,17 @@
 
 namespace mghlbm {
 
-// The transposed stencil of a grid node q: slot s holds the coefficients its
-// neighbour p (at slot s of q) applies to q, i.e. p's own slot 8 - s; bit s
+// The transposed stencil of a grid node q: the slots s whose neighbour p (at
+// slot s of q) applies a coefficient to q (p's own slot 8 - s), in slot order,
+// slot s[i] with (C, Gx, Gy) = w[i], padded with q itself at zero weight; bit i
 // of star is set when p reads q's structured-derived value instead of q's f
 // (both on the outer ring, Eq.(postcollision2_u)). Nodes with equal
 // transposed stencils share one class.
 template <class R>
 struct AdjClass {
-  R Gx[NSLOT];
-  R Gy[NSLOT];
-  R C[NSLOT];
-  int star;
+  R w[NLIST][3];
+  int s[NLIST], star;
   int type;  // NodeType of q
-  // the same without the empty slots, in slot order: slot li_s[i] with (C,
-  // Gx, Gy) = li_w[i] and bit i of li_star, padded with q itself at zero weight
-  R li_w[NLIST][3];
-  int li_s[NLIST], li_star;
 };
 
 // Everything the adjoint kernels of one reverse step read, by value.
@@ -55,7 +50,6 @@ struct AdjCtx {
   const int *iface;
   const int *wall_nodes;    // ids of the wall nodes
   const int *widx;          // per grid node: its index among the wall nodes, -1 otherwise
-  const unsigned char *ntype;  // per grid node: NodeType
   const int *acls;          // per grid node: transposed stencil class
   const AdjClass<R> *atab;
   const double *wall_nrm;   // [2][nnode]: sum over a wall node's edges of (len/2) n

@@ -392,14 +392,14 @@ __global__ __launch_bounds__(A::NT) void k_adj_substeps(AdjCtx<T, R> c, const R 
 #pragma unroll
   for (int q = 0; q < 9; ++q) f[q] = in && dist < count ? Um[q * N + p] : R(1);
   const AdjClass<R> &cl = c.atab[in ? c.acls[p] : 0];
-  const int typ = in ? cl.type : NODE_INTERIOR, star = in ? cl.li_star : 0;
+  const int typ = in ? cl.type : NODE_INTERIOR, star = in ? cl.star : 0;
   // dt c_q.G of the four distinct directions, and -dt/tau C, per entry
   R k1[NLIST], k2[NLIST], k5[NLIST], k6[NLIST], kc[NLIST];
   int row[NLIST];
 #pragma unroll
   for (int i = 0; i < NLIST; ++i) {
-    const int s = cl.li_s[i];
-    const R cc = cl.li_w[i][0], gx = cl.li_w[i][1], gy = cl.li_w[i][2];
+    const int s = cl.s[i];
+    const R cc = cl.w[i][0], gx = cl.w[i][1], gy = cl.w[i][2];
     k1[i] = c.dt * gx;
     k2[i] = c.dt * gy;
     k5[i] = c.dt * (gx + gy);

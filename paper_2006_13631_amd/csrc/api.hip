@@ -1876,20 +1876,21 @@ class Case final : public CaseBase {
     HIPCHK(upload(&wall_nrm_, nrm.data(), nrm.size() * sizeof(double)));
     std::vector<int> widx(N, -1);
     for (size_t w = 0; w < wn.size(); ++w) widx[wn[w]] = (int)w;
-    std::vector<unsigned char> ntype(N);
-    for (int p = 0; p < N; ++p) ntype[p] = (unsigned char)grid_.type[p];
     HIPCHK(upload(&widx_, widx.data(), widx.size() * sizeof(int)));
-    HIPCHK(upload(&ntype_, ntype.data(), ntype.size()));
     n_wall_ = (int)wn.size();
     // transposed stencils: slot s of node q holds what its neighbour at slot
     // s applies to q (the neighbour's slot 8 - s), deduplicated into classes
     {
-      std::vector<AdjClass<double>> atab;
+      struct Stencil {
+        double Gx[NSLOT], Gy[NSLOT], C[NSLOT];
+        int star, type;  // star: by slot
+      };
+      std::vector<Stencil> atab;
       std::vector<int> acls(N);
       std::map<std::string, int> seen;
       for (int q = 0; q < N; ++q) {
         const int i = q % cfg_.nux, j = q / cfg_.nux;
-        AdjClass<double> a;
+        Stencil a;
         std::memset(&a, 0, sizeof(a));
         a.type = grid_.type[q];
         for (int s = 0; s < NSLOT; ++s) {
@@ -1913,26 +1914,21 @@ class Case final : public CaseBase {
       std::vector<AdjClass<R>> at(atab.size());
       for (size_t k = 0; k < atab.size(); ++k) {
         std::memset(&at[k], 0, sizeof(at[k]));
-        for (int s = 0; s < NSLOT; ++s) {
-          at[k].Gx[s] = (R)atab[k].Gx[s];
-          at[k].Gy[s] = (R)atab[k].Gy[s];
-          at[k].C[s] = (R)atab[k].C[s];
-        }
-        at[k].star = atab[k].star;
         at[k].type = atab[k].type;
         // (a node's neighbours are those of its own stencil: at most NLIST entries)
         int n = 0;
         for (int sl = 0; sl < NSLOT; ++sl) {
-          if (at[k].C[sl] == R(0) && at[k].Gx[sl] == R(0) && at[k].Gy[sl] == R(0)) continue;
+          const R cc = (R)atab[k].C[sl], gx = (R)atab[k].Gx[sl], gy = (R)atab[k].Gy[sl];
+          if (cc == R(0) && gx == R(0) && gy == R(0)) continue;
           if (n == NLIST) return fail(HLBM_E_ARG, "a grid node has more than seven stencil entries");
-          at[k].li_s[n] = sl;
-          at[k].li_w[n][0] = at[k].C[sl];
-          at[k].li_w[n][1] = at[k].Gx[sl];
-          at[k].li_w[n][2] = at[k].Gy[sl];
-          if ((at[k].star >> sl) & 1) at[k].li_star |= 1 << n;
+          at[k].s[n] = sl;
+          at[k].w[n][0] = cc;
+          at[k].w[n][1] = gx;
+          at[k].w[n][2] = gy;
+          if ((atab[k].star >> sl) & 1) at[k].star |= 1 << n;
           ++n;
         }
-        for (; n < NLIST; ++n) at[k].li_s[n] = SELF_SLOT;
+        for (; n < NLIST; ++n) at[k].s[n] = SELF_SLOT;
       }
       HIPCHK(upload(&atab_, at.data(), at.size() * sizeof(AdjClass<R>)));
       HIPCHK(upload(&acls_, acls.data(), acls.size() * sizeof(int)));
@@ -1962,7 +1958,6 @@ class Case final : public CaseBase {
     c.iface = iface_;
     c.wall_nodes = wall_nodes_;
     c.widx = widx_;
-    c.ntype = ntype_;
     c.acls = acls_;
     c.atab = atab_;
     c.wall_nrm = wall_nrm_;
@@ -2199,7 +2194,6 @@ class Case final : public CaseBase {
   R *Vend_ = nullptr;  // outflow ends: adjoints of the two rows at each end
   unsigned char *zf_ = nullptr;
   int *wall_nodes_ = nullptr, *widx_ = nullptr, *acls_ = nullptr;
-  unsigned char *ntype_ = nullptr;
   AdjClass<R> *atab_ = nullptr;
   R *wtape_[2] = {nullptr, nullptr};
   int n_wall_ = 0, n_adj_classes_ = 0;

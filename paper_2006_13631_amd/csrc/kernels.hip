@@ -143,11 +143,11 @@ __global__ __launch_bounds__(256) void kb_stream_collide(const CaseView<T, R> *_
 // bases (the general path's wrapped 64-bit addresses and its two integer
 // divisions per node made the kernel instruction-bound in FP32 and FP16);
 // the others follow pull_index and pull_source.
-template <class T, class R, int NT>
+template <class T, class R>
 struct TwoStepTile {
   static constexpr int TX = kTwoStepTX, TY = kTwoStepTY, LX = TX + 2, LY = TY + 2, LN = LX * LY;
+  static constexpr int NT = TX * TY;             // lanes: one per node of the tile
   static constexpr int P1 = (LN + NT - 1) / NT;  // nodes of the tile and its ring per lane
-  static_assert(TX * TY <= NT, "at most one output node per lane");
 
   // whether every node the tile and its ring pull from lies inside the
   // lattice, at a byte offset of less than 2^32 in its plane
@@ -210,7 +210,7 @@ struct TwoStepTile {
                                                 const R *s) {
     const int ox = threadIdx.x % TX, oy = threadIdx.x / TX;
     const int x = tx0 + ox, y = ty0 + oy;
-    if (oy >= TY || x >= v.nx || y >= v.ny) return;
+    if (x >= v.nx || y >= v.ny) return;
     if (band && x >= v.bx0 && x <= v.bx1 && y >= v.by0 && y <= v.by1) return;
     const int l = (oy + 1) * LX + ox + 1;
     R g[9], rho;
@@ -250,10 +250,10 @@ struct TwoStepTile {
 // addresses a power of two apart (which share HBM channels). ndon leading
 // workgroups compute the interface donors, as in k_stream_collide.
 template <class T, class R>
-__global__ __launch_bounds__(512) void k_stream_collide2(CaseView<T, R> v, int tiles_x, int stagger, int ndon) {
-  constexpr int NT = 512;
-  using Tile = TwoStepTile<T, R, NT>;
-  constexpr int TX = Tile::TX, LX = Tile::LX, LN = Tile::LN, P1 = Tile::P1;
+__global__ __launch_bounds__(kTwoStepTX * kTwoStepTY) void k_stream_collide2(CaseView<T, R> v, int tiles_x, int stagger,
+                                                                             int ndon) {
+  using Tile = TwoStepTile<T, R>;
+  constexpr int TX = Tile::TX, LX = Tile::LX, LN = Tile::LN, P1 = Tile::P1, NT = Tile::NT;
   __shared__ R s[9 * LN];
   int t = (int)blockIdx.x - ndon;
   if (t < 0) {
@@ -381,7 +381,7 @@ constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;
 // f* = f^eq,s + (1 - 1/(2 tau_s)) f^neq,s and f^neq* from the lattice at t_{k+1}
 // (pre-collision), held over the n sub-steps (Eq.(postcollision2_u)). Four
 // consecutive lanes take the four bilinear donors of one node and combine
-// their weighted moments with two shuffles.
+// their weighted moments with register moves between lanes.
 template <class T, class R>
 __device__ __forceinline__ void interface_donors_block(const CaseView<T, R> &v, const T *__restrict__ A, int64_t k,
                                                        int bx) {
