@@ -1285,6 +1285,8 @@ class Case final : public CaseBase {
       best_ms = 3e38f;
       int best = 0;
       for (int sv = 0; sv < kSubstepVariantsSingle; ++sv) {
+        // a tile that gives way to another is not another choice
+        if (fitted_substep_variant(sv, [&](int t2) { return substep_tiles(t2, cfg_.nux, cfg_.nuy); }) != sv) continue;
         const int blk = substep_block(sv);
         const float ms = timed(s_grid_, [&] {
           for (int m = 0; m < d_.n; m += blk)
@@ -2398,7 +2400,8 @@ class Batch final : public CaseBase {
         }
     const hlbm_tuning after_l = best;
     for (int sv = 0; sv < kSubstepVariants; ++sv)
-      if (sv != (after_l.substep_variant < 0 ? kBatchSubstepVariant : after_l.substep_variant)) {
+      if (fitted(sv, all) == sv &&
+          sv != fitted(after_l.substep_variant < 0 ? kBatchSubstepVariant : after_l.substep_variant, all)) {
         hlbm_tuning c = cand(after_l);
         c.substep_variant = sv;
         trial(c);
@@ -2441,6 +2444,7 @@ class Batch final : public CaseBase {
         for (int sv = mode ? kPersistentFirst : 0; sv <= (mode ? kPersistentLast : kSubstepVariants - 1) &&
                                                     rc == HLBM_OK;
              ++sv) {
+          if (fitted(sv, tail) != sv) continue;
           tuning_ = best;
           tuning_.persistent = mode;
           tuning_.substep_variant = sv;
@@ -2547,7 +2551,10 @@ class Batch final : public CaseBase {
   // the sub-step kernel for this set of running cases
   int variant_for(const std::vector<int> &act) const {
     const int sv = (tuning_.tail_variant >= 0 && is_tail(act)) ? tuning_.tail_variant : tuning_.substep_variant;
-    return fitted_substep_variant(sv < 0 ? kBatchSubstepVariant : sv, [&](int s) {
+    return fitted(sv < 0 ? kBatchSubstepVariant : sv, act);
+  }
+  int fitted(int variant, const std::vector<int> &act) const {
+    return fitted_substep_variant(variant, [&](int s) {
       int64_t n = 0;
       for (int c : act) {
         const CaseView<T, R> v = cases_[c]->batched_view();
