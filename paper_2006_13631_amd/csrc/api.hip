@@ -325,6 +325,7 @@ class Case final : public CaseBase {
         HIPCHK(upload(&m_blist_, grid_.blist.data(), std::max<size_t>(1, grid_.blist.size()) * sizeof(int)));
       }
       std::vector<GridClass<R>> tab(grid_.classes.size());
+      std::vector<GridList<R>> lst(grid_.classes.size());
       for (size_t i = 0; i < tab.size(); ++i) {
         const GridClass<double> &g = grid_.classes[i];
         GridClass<R> &t = tab[i];
@@ -343,16 +344,17 @@ class Case final : public CaseBase {
             err = "a grid node has more than seven stencil entries";
             return HLBM_E_ARG;
           }
-          t.li_s[n] = s;
-          t.li_w[n][0] = t.C[s];
-          t.li_w[n][1] = t.Gx[s];
-          t.li_w[n][2] = t.Gy[s];
+          lst[i].s[n] = s;
+          lst[i].w[n][0] = t.C[s];
+          lst[i].w[n][1] = t.Gx[s];
+          lst[i].w[n][2] = t.Gy[s];
           ++n;
         }
-        for (; n < NLIST; ++n) t.li_s[n] = SELF_SLOT;
+        for (; n < NLIST; ++n) lst[i].s[n] = SELF_SLOT;
       }
       if (!grid_.mesh) {
         HIPCHK(upload(&tab_, tab.data(), tab.size() * sizeof(GridClass<R>)));
+        HIPCHK(upload(&lst_, lst.data(), lst.size() * sizeof(GridList<R>)));
         // node codes: 4 * class + type (static: the grid moves rigidly)
         std::vector<int> code(grid_.cls.size());
         for (size_t p = 0; p < code.size(); ++p) {
@@ -1641,6 +1643,7 @@ class Case final : public CaseBase {
       v.gy = dgy_;
       v.ncode = ncode_;
       v.tab = tab_;
+      v.lst = lst_;
       v.iface = iface_;
       if (grid_.mesh) {
         v.mesh = 1;
@@ -2144,6 +2147,7 @@ class Case final : public CaseBase {
   int gcur_ = 0;
   R *star_f_ = nullptr, *star_n_ = nullptr;
   GridClass<R> *tab_ = nullptr;
+  GridList<R> *lst_ = nullptr;
   int *ncode_ = nullptr, *iface_ = nullptr;
   // unstructured grid (device copies of the HostGrid mesh fields)
   int *m_row_ = nullptr, *m_col_ = nullptr, *m_type_ = nullptr, *m_tri_ = nullptr;

@@ -50,10 +50,17 @@ struct GridClass {
   R Gy[NSLOT];      // y weights of the streaming matrix
   R C[NSLOT];       // collision matrix C_ik
   int type;         // NodeType
-  // the same weights without the empty slots, in slot order: slot li_s[i]
-  // with (C, Gx, Gy) = li_w[i], padded with the node itself at zero weight
-  R li_w[NLIST][3];
-  int li_s[NLIST];
+};
+
+// The same weights without the empty slots, in slot order: slot s[i] with (C,
+// Gx, Gy) = w[i], padded with the node itself at zero weight; what a kernel
+// with a node per lane reads. Apart from the class, which every node's
+// stencil is compared by when the grid is built (with both in one a case with
+// a 1024 x 256 grid took 25.8 ms to create, 21.7 so).
+template <class R>
+struct GridList {
+  R w[NLIST][3];
+  int s[NLIST];
 };
 
 struct WallEdge {

@@ -55,6 +55,7 @@ struct CaseView {
   // (-1: no class), so a kernel learns a node's type and stencil in one load
   const int *ncode;
   const GridClass<R> *tab;
+  const GridList<R> *lst;  // the classes' compact lists
   const int *iface;
   const WallEdge *wall;
   // unstructured grid (mesh != 0; the split-quad fields above unused):

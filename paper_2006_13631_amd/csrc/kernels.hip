@@ -750,7 +750,7 @@ constexpr size_t fixed_lds_bytes() {
 template <class R, class G, int H, int NT, bool DB>
 __device__ __forceinline__ void grid_fixed_block(
     const R *__restrict__ f, R *__restrict__ fout, const R *__restrict__ star_f, const int *__restrict__ ncode,
-    const GridClass<R> *__restrict__ tab, int nux, int nuy, int tiles_x, int t, R dt, R dt_tau,
+    const GridList<R> *__restrict__ lst, int nux, int nuy, int tiles_x, int t, R dt, R dt_tau,
     const R *__restrict__ uw, int64_t k, int n_sub, int m0, int count, R *__restrict__ tape,
     R *__restrict__ wtape, const int *__restrict__ widx, int nwall) {
   constexpr int TX = G::TX, TY = G::TY, RX = G::RX, RN = G::RN;
@@ -773,14 +773,14 @@ __device__ __forceinline__ void grid_fixed_block(
 #pragma unroll
   for (int q = 0; q < 9; ++q) own[q] = in ? f[q * N + p] : R(0);
   const int code = in ? ncode[p] : -1, typ = code & 3;
-  const GridClass<R> &cl = tab[code >= 0 ? code >> 2 : 0];
+  const GridList<R> &cl = lst[code >= 0 ? code >> 2 : 0];
   const bool iface = code >= 0 && typ == NODE_INTERFACE;
   const int ring = idx < RN ? ring_slot<G>(gi, gj, rx, ry, nux, nuy) : -1;
 #pragma unroll
   for (int i = 0; i < NLIST; ++i) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) w[i][a] = cl.li_w[i][a];
-    const int s = cl.li_s[i], di = s % 3 - 1, dj = s / 3 - 1;
+    for (int a = 0; a < 3; ++a) w[i][a] = cl.w[i][a];
+    const int s = cl.s[i], di = s % 3 - 1, dj = s / 3 - 1;
     row[i] = (idx + dj * RX + di) * NS;
     if (iface) {
       const int rs = ring_slot<G>(gi + di, gj + dj, rx + di, ry + dj, nux, nuy);
@@ -909,7 +909,15 @@ struct SubstepShape {
   static constexpr int NT = NTv;
   static constexpr int H = Hv;  // sub-steps per launch, and the halo width
   static constexpr bool FIXED = NTv >= G::RN;  // one node per lane for the whole launch
+  template <class R>  // the weights it reads
+  using Table = std::conditional_t<FIXED, GridList<R>, GridClass<R>>;
 };
+// ... of a case
+template <class SV, class T, class R>
+__host__ __device__ __forceinline__ const typename SV::template Table<R> *substep_table(const CaseView<T, R> &v) {
+  if constexpr (SV::FIXED) return v.lst;
+  else return v.tab;
+}
 template <class R, class SV, bool BATCH = false>
 constexpr size_t variant_lds_bytes() {
   using G = typename SV::G;
@@ -933,9 +941,9 @@ template <> struct SubstepVariant<10> : SubstepShape<32, 8, 448, 2> {};
 template <class R, int V>
 __global__ __launch_bounds__(SubstepVariant<V>::NT) void k_grid_substeps(
     const R *__restrict__ f, R *__restrict__ fout, const R *__restrict__ star_f, const R *__restrict__ star_n,
-    const int *__restrict__ ncode, const GridClass<R> *__restrict__ tab, int nux, int nuy, int tiles_x, int ntiles,
-    R dt, R dt_tau, const R *__restrict__ uw, const int64_t *__restrict__ dk, int n_sub, int m0, int count,
-    R *__restrict__ tape, R *__restrict__ wtape, const int *__restrict__ widx, int nwall) {
+    const int *__restrict__ ncode, const typename SubstepVariant<V>::template Table<R> *__restrict__ tab, int nux,
+    int nuy, int tiles_x, int ntiles, R dt, R dt_tau, const R *__restrict__ uw, const int64_t *__restrict__ dk,
+    int n_sub, int m0, int count, R *__restrict__ tape, R *__restrict__ wtape, const int *__restrict__ widx, int nwall) {
   using SV = SubstepVariant<V>;
   const int b = blockIdx.x;  // tiles are dealt to the eight XCDs in contiguous bands
   const int t = (ntiles % 8 == 0) ? (b % 8) * (ntiles / 8) + (b / 8) : b;
@@ -966,7 +974,7 @@ __attribute__((amdgpu_waves_per_eu(1, V == 6 && sizeof(R) == 8 ? 2 : 8))) void k
   const int tiles_x = (v.nux + SV::G::TX - 1) / SV::G::TX;
   if constexpr (SV::FIXED)
     grid_fixed_block<R, typename SV::G, kSubstepBlock, SV::NT, false>(
-        v.grid[cur ^ (i & 1)], v.grid[cur ^ ((i + 1) & 1)], v.star_f, v.ncode, v.tab, v.nux, v.nuy, tiles_x, it.y,
+        v.grid[cur ^ (i & 1)], v.grid[cur ^ ((i + 1) & 1)], v.star_f, v.ncode, v.lst, v.nux, v.nuy, tiles_x, it.y,
         v.dt_u, v.dt_over_tau_u, v.uw, k, v.n_sub, m0, min(kSubstepBlock, v.n_sub - m0), nullptr, nullptr, nullptr,
         0);
   else
@@ -1992,14 +2000,14 @@ void Kernels<T, R>::grid_substeps_v(const CaseView<T, R> &v, const R *f, R *fout
   if (start || stop)
     hipExtLaunchKernelGGL((k_grid_substeps<R, V>), dim3(tiles_x * tiles_y), dim3(SV::NT), lds, s, start, stop, 0,
                           f, fout,
-                          (const R *)v.star_f, (const R *)v.star_n, v.ncode, v.tab, v.nux, v.nuy, tiles_x,
-                          tiles_x * tiles_y, v.dt_u, v.dt_over_tau_u, v.uw, (const int64_t *)v.dk, v.n_sub, m0,
+                          (const R *)v.star_f, (const R *)v.star_n, v.ncode, substep_table<SV>(v), v.nux, v.nuy,
+                          tiles_x, tiles_x * tiles_y, v.dt_u, v.dt_over_tau_u, v.uw, (const int64_t *)v.dk, v.n_sub, m0,
                           count, tape, wtape, widx, nwall);
   else
     hipLaunchKernelGGL((k_grid_substeps<R, V>), dim3(tiles_x * tiles_y), dim3(SV::NT), lds, s, f, fout,
-                       (const R *)v.star_f,
-                       (const R *)v.star_n, v.ncode, v.tab, v.nux, v.nuy, tiles_x, tiles_x * tiles_y, v.dt_u,
-                       v.dt_over_tau_u, v.uw, (const int64_t *)v.dk, v.n_sub, m0, count, tape, wtape, widx, nwall);
+                       (const R *)v.star_f, (const R *)v.star_n, v.ncode, substep_table<SV>(v), v.nux, v.nuy, tiles_x,
+                       tiles_x * tiles_y, v.dt_u, v.dt_over_tau_u, v.uw, (const int64_t *)v.dk, v.n_sub, m0, count,
+                       tape, wtape, widx, nwall);
 }
 
 template <class T, class R>
