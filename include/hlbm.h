@@ -416,8 +416,9 @@ int hlbm_set_state(hlbm_t *h, int32_t case_id, int32_t which,
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * as hlbm_get_state for which = HLBM_STATE_LATTICE or HLBM_STATE_GRID (the
  * same bits), but it calls no hipMalloc, hipFree or other allocating
- * routine. hlbm_get_state converts the state to FP64 in a device buffer it
- * allocates for the call; this variant converts one population plane at a
+ * routine. hlbm_get_state converts a lattice to FP64 in a device buffer of at
+ * most 16 MiB, which the handle allocates at its first such read and keeps;
+ * this variant converts one population plane at a
  * time, in pieces of at most HLBM_NOALLOC_SCRATCH_BYTES, in a static device
  * buffer of that size which each GPU the library runs on holds until the
  * process ends, and copies each piece to host_buf before converting the
